@@ -7,10 +7,10 @@
 //   weights  dW    = dG^T . [x | h~_prev]                   (A, B I-contiguous)
 //   input    dx    = dG . W_x                               (B I-contiguous)
 // A loader reports whether its reduction index k is the contiguous one
-// (kKMajor), hands out single elements to the fp32 engine (at) and, for
-// the bf16 engine, has a per-thread Tile state that precomputes everything
-// that does not change along K (row offsets, masks, sources) so that the
-// K loop issues plain 16-byte loads with no branches.
+// (kKMajor) and, for the bf16 engine, has a per-thread Tile state that
+// precomputes everything that does not change along K (row offsets, masks,
+// sources) so that the K loop issues plain 16-byte loads with no branches.
+// (The fp32 engine, gemm_f32.h, has its own state for the same loaders.)
 //
 // bf16 engine (gfx950 MFMA, v_mfma_f32_32x32x16_bf16, fp32 accumulate):
 //  * block tile BM x BN, K tile 64, waves arranged (BM/WM) x (BN/WN), each
@@ -98,13 +98,6 @@ struct KRows2 {
   // (stride gstride = H) of 64 consecutive hidden units.
   int gstride = 0;
 
-  __device__ __forceinline__ float at(int i, int k) const {
-    if (i >= rows || k >= K) return 0.0f;
-    if (k < K0) return elem<E>::to_f32(p0[static_cast<size_t>(i) * ld0 + k]);
-    if (mask1 && mask1[i]) return 0.0f;
-    return elem<E>::to_f32(p1[static_cast<size_t>(i) * ld1 + (k - K0)]);
-  }
-
   // Per-thread state of the bf16 engine for a ROWS x 64 tile loaded by NT
   // threads: thread t always loads chunk (t & 7) of rows (t >> 3) + u*NT/8.
   // Requires K0 % 64 == 0 (a K tile never straddles the two sources),
@@ -170,13 +163,6 @@ struct ICols2 {
   __device__ __forceinline__ const E* row1(int k) const {
     return k < kswitch ? p1a + static_cast<size_t>(k) * ld1 : p1b + static_cast<size_t>(k - kswitch) * ld1;
   }
-  __device__ __forceinline__ float at(int i, int k) const {
-    if (i >= I || k >= K) return 0.0f;
-    if (i < I0) return elem<E>::to_f32(p0[static_cast<size_t>(k) * ld0 + i]);
-    if (mask1 && mask1[k]) return 0.0f;
-    return elem<E>::to_f32(row1(k)[i - I0]);
-  }
-
   // Per-thread state of the bf16 engine for a ROWS x 64 tile: the tile holds
   // (ROWS/8) x 8 blocks of 8 i x 8 k; thread t loads block (i-chunk t >> 3,
   // k-chunk t & 7) (+ NT/8 i-chunks per extra block), i.e. 8 rows k of 8
@@ -366,58 +352,6 @@ __device__ __forceinline__ void store_acc(const Epi& epi, const f32x16_t (&acc)[
       }
 }
 
-// ------------------------------------------------------ fp32 FMA engine
-// 64 x 64 tile, K tile 16, 256 threads, 4 x 4 outputs per thread.
-// Used for the fp32 path, where exactness matters more than speed.
-template <class AL, class BL, class Epi>
-__global__ void __launch_bounds__(256) gemm_f32_fma(AL al, BL bl, Epi epi, int M, int N, int K, int ktiles_per_split) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-  const int split = blockIdx.z;
-  const int nkt = (K + BK - 1) / BK;
-  const int kt0 = split * ktiles_per_split;
-  const int kt1 = min(nkt, kt0 + ktiles_per_split);
-  float acc[4][4] = {};
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int k0 = kt * BK;
-    // 64 x 16 elements per operand, 4 per thread; the contiguous index varies fastest
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * 256;
-      int i, k;
-      if (AL::kKMajor) { i = e / BK; k = e % BK; } else { k = e / BM; i = e % BM; }
-      As[k][i] = al.at(m0 + i, k0 + k);
-      if (BL::kKMajor) { i = e / BK; k = e % BK; } else { k = e / BN; i = e % BN; }
-      Bs[k][i] = bl.at(n0 + i, k0 + k);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) a[r] = As[k][ty + 16 * r];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) b[r] = Bs[k][tx + 16 * r];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acc[r][s] = fmaf(a[r], b[s], acc[r][s]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int i = m0 + ty + 16 * r, j = n0 + tx + 16 * s;
-      if (i < M && j < N) epi(i, j, acc[r][s], split);
-    }
-}
-
 // ------------------------------------------------------ bf16 MFMA engine
 
 constexpr int kGroupM = 4;
@@ -576,15 +510,6 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 1)
 }
 
 // ------------------------------------------------------------ launchers
-
-template <class AL, class BL, class Epi>
-inline void launch_gemm_f32(const AL& al, const BL& bl, const Epi& epi, int M, int N, int K, int splits,
-                            hipStream_t s) {
-  const int nkt = (K + 15) / 16;
-  const int kps = (nkt + splits - 1) / splits;
-  dim3 grid((M + 63) / 64, (N + 63) / 64, splits);
-  hipLaunchKernelGGL((gemm_f32_fma<AL, BL, Epi>), grid, dim3(256), 0, s, al, bl, epi, M, N, K, kps);
-}
 
 // Tile configurations of the bf16 engines: block tile, waves (x 64 threads).
 //   kDma256    256 x 256, 8 waves, buffer loads straight to LDS (gemm_kk.h for

@@ -3,6 +3,7 @@
 
 #include <type_traits>
 
+#include "gemm_f32.h"
 #include "gemm_kk.h"
 
 namespace o5 {
@@ -10,7 +11,6 @@ namespace o5 {
 // --------------------------------------------------------------- planning
 
 struct GemmPlan {
-  bool bf16;
   BfTile tile;
   int splits;
   int bn;  // column tile of the K-contiguous engine: 256 or 128
@@ -26,12 +26,11 @@ inline int cdiv(long long a, long long b) { return static_cast<int>((a + b - 1) 
 // 256 tiles split in two, the narrower tile needing 1.5x the operand bytes
 // per MFMA.)
 inline GemmPlan plan_gemm(bool bf16, int M, int N, int K) {
-  GemmPlan p{bf16, BfTile::kDma256, 1, 256};
+  GemmPlan p{BfTile::kDma256, 1, 256};
   if (!bf16) {
-    const int tiles = cdiv(M, 64) * cdiv(N, 64);
-    const int nkt = cdiv(K, 16);
-    int s = cdiv(512, tiles);
-    s = std::min(s, std::max(1, nkt / 8));
+    // two blocks per CU, every split with at least 128 k
+    const long long tiles = f32_tiles(M, N);
+    const int s = static_cast<int>(std::min<long long>((512 + tiles - 1) / tiles, std::max(1, K / 128)));
     p.splits = std::max(1, std::min(s, 16));
     return p;
   }
@@ -63,27 +62,24 @@ inline bool dma_ok(const ICols2<E>& l) { return l.mask1 == nullptr; }
 template <class AL, class BL, class Epi>
 inline void run_gemm(const GemmPlan& p, const AL& al, const BL& bl, const Epi& epi, int M, int N, int K,
                      hipStream_t s) {
-  if constexpr (AL::kBf16 && BL::kBf16) {
-    if (p.bf16) {
-      if constexpr (std::is_same_v<AL, KRows2<uint16_t>> && std::is_same_v<BL, KRows2<uint16_t>>) {
-        if (p.tile == BfTile::kDma256 && kk_fits(al) && kk_fits(bl)) {
-          if (p.bn == 128)
-            launch_gemm_kk<128>(al, bl, epi, M, N, K, p.splits, s);
-          else
-            launch_gemm_kk<256>(al, bl, epi, M, N, K, p.splits, s);
-          return;
-        }
-      }
-      if (p.tile == BfTile::kDma256 && dma_ok(al) && dma_ok(bl)) {
-        launch_gemm_bf16_dma(al, bl, epi, M, N, K, p.splits, s);
+  static_assert(AL::kBf16 == BL::kBf16, "operands of one type");
+  if constexpr (AL::kBf16) {
+    if constexpr (std::is_same_v<AL, KRows2<uint16_t>> && std::is_same_v<BL, KRows2<uint16_t>>) {
+      if (p.tile == BfTile::kDma256 && kk_fits(al) && kk_fits(bl)) {
+        if (p.bn == 128)
+          launch_gemm_kk<128>(al, bl, epi, M, N, K, p.splits, s);
+        else
+          launch_gemm_kk<256>(al, bl, epi, M, N, K, p.splits, s);
         return;
       }
-      launch_gemm_bf16(al, bl, epi, M, N, K, p.splits,
-                       p.tile == BfTile::kDma256 ? BfTile::k256x256w8 : p.tile, s);
-      return;
     }
+    if (p.tile == BfTile::kDma256 && dma_ok(al) && dma_ok(bl))
+      launch_gemm_bf16_dma(al, bl, epi, M, N, K, p.splits, s);
+    else
+      launch_gemm_bf16(al, bl, epi, M, N, K, p.splits, p.tile == BfTile::kDma256 ? BfTile::k256x256w8 : p.tile, s);
+  } else {
+    launch_gemm_f32(al, bl, epi, M, N, K, p.splits, s);
   }
-  launch_gemm_f32(al, bl, epi, M, N, K, p.splits, s);
 }
 
 }  // namespace o5

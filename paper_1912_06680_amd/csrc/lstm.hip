@@ -18,7 +18,7 @@
 //   GEMM  dx = dG . W_x                                     (M = T B, N = D, K = 4H), optional
 //   db    = fixed-order sum of the per-block column sums.
 //
-// fp32 path: the FMA engine; bf16 path: the MFMA engine, with h, the saved
+// fp32 path: fp32 matrix products; bf16 path: bf16 ones, with h, the saved
 // gates and dG stored in bf16 and everything else in fp32.
 #include "gemm_plan.h"
 #include "reduce.h"

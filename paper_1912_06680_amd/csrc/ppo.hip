@@ -929,7 +929,7 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
                          w.wsplits, A1, A1p, H, wpart, dWp);
     }
   } else {
-    if (unit == nullptr) {  // dh = dz Wp  (fp32 FMA engine)
+    if (unit == nullptr) {  // dh = dz Wp
       KRows2<float> al{dz, nullptr, nullptr, A1, 0, A1, A1, N};
       ICols2<E> bl{Wp, nullptr, nullptr, nullptr, H, 0, H, H, A1, 0};
       EpiStoreF32 epi{dh, H, 0};
