@@ -18,9 +18,13 @@
 //   GEMM  dx = dG . W_x                                     (M = T B, N = D, K = 4H), optional
 //   db    = fixed-order sum of the per-block column sums.
 //
+// Small and middle batches (bf16) and most fp32 shapes take each step, product
+// and cell together, in one launch of lstm_step.h (rules: step_fwd, step_bwd_mf).
+//
 // fp32 path: fp32 matrix products; bf16 path: bf16 ones, with h, the saved
 // gates and dG stored in bf16 and everything else in fp32.
 #include "gemm_plan.h"
+#include "lstm_step.h"
 #include "reduce.h"
 
 namespace o5 {
@@ -456,6 +460,20 @@ __global__ void __launch_bounds__(256) transpose_rows(int T, int B, int Bp, int 
   }
 }
 
+// dst [C][R] = src [R][C] transposed, fp32, R and C multiples of 64: one 64 x
+// 64 tile per block through LDS.
+__global__ void __launch_bounds__(256) transpose_f32(int R, int C, const float* __restrict__ src,
+                                                     float* __restrict__ dst) {
+  __shared__ float t[64][65];
+  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) t[w + 4 * i][lane] = src[static_cast<size_t>(r0 + w + 4 * i) * C + c0 + lane];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) dst[static_cast<size_t>(c0 + w + 4 * i) * R + r0 + lane] = t[lane][w + 4 * i];
+}
+
 // B rounded up to 64, the time padding of the weight gradient's K: column
 // t * Bp + b of [x | h~]^T holds sample b of step t (zero for b >= B).
 static inline int time_pad(int B) { return cdiv(B, 64) * 64; }
@@ -467,8 +485,46 @@ static inline dim3 transpose_grid(int C, long long rows) {
 
 // ---------------------------------------------------------------- layouts
 
+// Whether a forward step runs as one launch of lstm_step.h.  Its cost grows
+// with its blocks (each reads its own operands; 64 x 64 tiles), the separate
+// product's with its 256 x 256 (bf16) or 128 x 128 (fp32) tiles, which reuse
+// operands better but need a grid that fills the chip.  us per step, one
+// launch against product and cell, D = H:
+//   bf16  H = 1024: 11.8 / 36 (B = 256), 31.5 / 43 (600: 640 blocks), 46 / 46 (1024)
+//         H = 2048: 33 / 58 (256: 512 blocks), 84 / 87 (600), 138 / 86 (1024)
+//         H = 4096: 44 / 73 (60), 67 / 89 (128: 512 blocks), 137 / 120 (256)
+//   fp32  H = 512: 44 / 57 (B = 1024), 179 / 164 (4096: 512 tiles)
+//         H = 1024: 43 / 65 (256), 300 / 302 (2048: 512 tiles)
+static bool step_fwd(o5_dtype dt, int B, int D, int H) {
+  if (!step::offsets_fit(dtype_size(dt), B, D, H)) return false;
+  if (dt == O5_F32) return static_cast<long long>(cdiv(B, 128)) * cdiv(4 * H, 128) < 512;
+  return static_cast<long long>(cdiv(B, 64)) * (H / step::UNITS) <= 768;
+}
+
+// Tile of the backward step's launch of lstm_step.h (16 MF rows x 16 MF
+// units), or 0 where the product (split over K) and the cell are launches of
+// their own.  Whole calls of 16 steps in us, one launch per step against two:
+//   bf16  H = 1024: 296 / 443 (B = 256: 256 blocks of 32 x 32), 854 / 709 (600)
+//         H = 2048: 463 / 651 (128), 823 / 818 (256: 512 blocks)
+//         H = 4096: 863 / 1190 (60), 1436 / 1454 (128: 512 blocks)
+//   fp32  H = 512: 296 / 242 (B = 60: 32 blocks, each with the whole K)
+//         H = 2048: 1259 / 1100 (60), 3680 / 3848 (256)
+//         H = 4096: 3581 / 3836 (60: 256 blocks), 13367 / 15008 (256)
+// In fp32 a few blocks each walk all of K on the matrix units, so the grid has
+// to fill the chip unless K is short; 64 x 64 tiles take 0.9 of the time of
+// four 32 x 32 ones, so the fewer rounds of the chip decide.
+static int step_bwd_mf(o5_dtype dt, int B, int D, int H) {
+  if (!step::offsets_fit(dtype_size(dt), B, D, H)) return 0;
+  const long long n2 = static_cast<long long>(cdiv(B, 32)) * (H / 32);
+  if (dt == O5_BF16) return n2 <= 384 ? 2 : 0;
+  if (n2 < 256 && H > 256) return 0;
+  const long long n4 = static_cast<long long>(cdiv(B, 64)) * (H / 64);
+  return n4 >= 256 && 3.6 * static_cast<double>((n4 + 255) / 256) < static_cast<double>((n2 + 255) / 256) ? 4 : 2;
+}
+
 struct FwdWs {
   size_t pre, h0e, total;
+  bool step;
   GemmPlan plan;
 };
 
@@ -476,9 +532,10 @@ static FwdWs fwd_ws(o5_dtype dt, int T, int B, int D, int H) {
   (void)T;
   FwdWs w;
   w.plan = plan_gemm(dt == O5_BF16, B, 4 * H, D + H);
+  w.step = step_fwd(dt, B, D, H);
   size_t o = 0;
   w.pre = o;
-  o += align_up(static_cast<size_t>(w.plan.splits) * B * 4 * H * sizeof(float));
+  if (!w.step) o += align_up(static_cast<size_t>(w.plan.splits) * B * 4 * H * sizeof(float));
   w.h0e = o;
   o += align_up(static_cast<size_t>(B) * H * dtype_size(dt));
   w.total = o;
@@ -488,6 +545,7 @@ static FwdWs fwd_ws(o5_dtype dt, int T, int B, int D, int H) {
 struct BwdWs {
   size_t dG, dc, rec, h0e, dbpart, dGT, XHT, WhT, total;
   int nbc;
+  int step_mf;  // tile of the one-launch backward step, or 0
   int Bp;       // B rounded up to the cell's row block (bf16 path: time-padded K of dW)
   size_t ldt;   // T * Bp, the leading dimension of dGT and XHT
   GemmPlan plan_dh, plan_dw, plan_dx;
@@ -510,7 +568,8 @@ static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H) {
   w.dc = o;
   o += align_up(static_cast<size_t>(B) * H * sizeof(float));
   w.rec = o;
-  o += align_up(static_cast<size_t>(w.plan_dh.splits) * B * H * sizeof(float));
+  w.step_mf = step_bwd_mf(dt, B, D, H);
+  if (w.step_mf == 0) o += align_up(static_cast<size_t>(w.plan_dh.splits) * B * H * sizeof(float));
   w.h0e = o;
   o += align_up(static_cast<size_t>(B) * H * dtype_size(dt));
   w.dbpart = o;
@@ -524,6 +583,8 @@ static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H) {
     o += align_up(static_cast<size_t>(D + H) * w.ldt * sizeof(uint16_t));
     w.WhT = o;
     o += align_up(static_cast<size_t>(H) * 4 * H * sizeof(uint16_t));
+  } else if (w.step_mf != 0) {
+    o += align_up(static_cast<size_t>(H) * 4 * H * sizeof(float));  // W_h^T
   }
   w.total = o;
   return w;
@@ -561,6 +622,17 @@ static int lstm_fwd_impl(int T, int B, int D, int H, const E* x, const E* Wx, co
     h0e = tmp;
   } else {
     h0e = h0;
+  }
+  if (w.step) {
+    // small and middle batches, and fp32: one launch per step, no partial sums
+    for (int t = 0; t < T; ++t) {
+      ktimer_begin(kSiteLstmFwdGemm, s);
+      launch_step_fwd(B, D, H, x + static_cast<size_t>(t) * B * D, t == 0 ? h0e : h + (t - 1) * BH, Wx, Wh, bias,
+                      t == 0 ? c0 : c + (t - 1) * BH, reset ? reset + static_cast<size_t>(t) * B : nullptr, h + t * BH,
+                      c + t * BH, gates ? gates + static_cast<size_t>(t) * B * 4 * H : nullptr, s);
+      ktimer_end(kSiteLstmFwdGemm, s);
+    }
+    return check_launch("o5_lstm_fwd");
   }
   if constexpr (sizeof(E) == 2) {
     if (w.plan.tile == BfTile::kDma256 && w.plan.splits == 1) {
@@ -623,7 +695,7 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
   float* dbpart = reinterpret_cast<float*>(ws + w.dbpart);
   E* dGT = kBf ? reinterpret_cast<E*>(ws + w.dGT) : nullptr;
   E* XHT = kBf ? reinterpret_cast<E*>(ws + w.XHT) : nullptr;
-  E* WhT = kBf ? reinterpret_cast<E*>(ws + w.WhT) : nullptr;
+  E* WhT = kBf || w.step_mf != 0 ? reinterpret_cast<E*>(ws + w.WhT) : nullptr;
   const E* h0e;
   if constexpr (kBf) {
     E* tmp = reinterpret_cast<E*>(ws + w.h0e);
@@ -635,6 +707,8 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
                        Wh, 4 * H, H, nullptr, WhT, static_cast<size_t>(4 * H));
   } else {
     h0e = h0;
+    if (w.step_mf != 0)
+      hipLaunchKernelGGL(transpose_f32, dim3(H / 64, 4 * H / 64), dim3(256), 0, s, 4 * H, H, Wh, WhT);
   }
   const dim3 pw_grid(cdiv(H, kPwCols), w.nbc);
   // the cell unrolls its loads of the recurrent GEMM's split partials up to NS
@@ -642,7 +716,24 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
               : w.plan_dh.splits <= 8 ? lstm_bwd_cell<E, 8>
                                       : lstm_bwd_cell<E, 16>;
   const bool fact = P != nullptr;
-  for (int t = T - 1; t >= 0; --t) {
+  for (int t = T - 1; t >= 0 && w.step_mf != 0; --t) {
+    // small and middle batches, and fp32: one launch per step
+    const bool last = t == T - 1;
+    ktimer_begin(kSiteLstmBwdCell, s);
+    const int rows = 16 * w.step_mf;
+    auto kernel = step::lstm_step_bwd<E, 2, 2>;
+    if constexpr (!kBf)
+      if (w.step_mf == 4) kernel = step::lstm_step_bwd<E, 4, 4>;
+    hipLaunchKernelGGL(kernel, dim3((w.Bp / rows) * (H / rows)), dim3(step::NT), 0, s, B, w.Bp, H,
+                       fact ? P + static_cast<size_t>(t) * B * ldp : nullptr, Wf, fact ? ldp : 0,
+                       last ? nullptr : dG + (t + 1) * BG, WhT,
+                       reset && !last ? reset + static_cast<size_t>(t + 1) * B : nullptr,
+                       fact ? nullptr : dh + t * BH, last ? dhT : nullptr, last ? dcT : dc, dc, gates + t * BG,
+                       c + t * BH, t == 0 ? c0 : c + (t - 1) * BH, reset ? reset + static_cast<size_t>(t) * B : nullptr,
+                       dG + t * BG, dbpart, last ? 0 : 1, dGT, w.ldt, t * w.Bp);
+    ktimer_end(kSiteLstmBwdCell, s);
+  }
+  for (int t = T - 1; t >= 0 && w.step_mf == 0; --t) {
     const float* recp = nullptr;
     int S = w.plan_dh.splits;  // partial sums the cell adds
     if (fact) {
