@@ -300,7 +300,7 @@ def trace_summary(trace_dir, out_md, command, bench_log=None):
         us = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in fwd]
         timed, inst = us[-n:], us[-2 * n:-n]
         lines += ["", f"The timed steps of this run under the profiler: {line['ms_per_step']:.2f} ms per step. The "
-                      f"dominant kernel, the fused forward GEMM (`gemm_kk<256, true, EpiLstmCell<bf16>, bf16>`, grid "
+                      f"dominant kernel, the fused forward GEMM (`gemm_kk<256, 256, true, EpiLstmCell<bf16>, bf16>`, grid "
                       f"262144): its {n} launches inside the timed steps average {sum(timed) / n:.1f} µs in this "
                       f"trace, and bench.py's HIP events over the same steps gave "
                       f"{1e3 * line['roofline']['ms_per_launch']:.1f} µs per launch (`roofline.ms_per_launch`); "

@@ -1,10 +1,9 @@
 // bf16 MFMA GEMM for two K-contiguous operands (gfx950):
 //   C[i, j] = sum_k A(i, k) * B(j, k)  (+ epilogue), fp32 accumulate.
 //
-// Block tile 256 x BN (BN = 256, or 128 where 256 x 256 tiles would need a
-// K split to fill the chip), one block per CU, 8 waves, two per SIMD, so one
+// Block tile 256 x 256 (or 256 x 128, 320 x 256: Shape), one block per CU, 8 waves, two per SIMD, so one
 // wave's MFMAs run while the other issues copies or waits at a barrier: 2 x 4
-// waves of 128 x 64 for BN = 256, 4 x 2 waves of 64 x 64 for BN = 128.  (4
+// waves of 128 x 64 for 256 x 256 tiles.  (4
 // waves of 128 x 128, one per SIMD, each fragment read from LDS feeding four
 // MFMAs, measured a few percent slower overall.)
 //
@@ -50,13 +49,17 @@ constexpr int R256 = 256 / ROW_BYTES;  // rows per 256 bytes
 constexpr int NWAVES = 8;              // two per SIMD
 constexpr int NT = NWAVES * 64;
 
-// Block and wave tiling of a 256 x BN block tile: 256 x 256 (2 x 4 waves of
-// 128 x 64) or 256 x 128 (4 x 2 waves of 64 x 64).
-template <int BN_>
+// Block and wave tiling of a BM x BN block tile: 256 x 256 (2 x 4 waves of
+// 128 x 64), 256 x 128 (4 x 2 waves of 64 x 64) or 320 x 256 (2 x 4 waves of
+// 160 x 64).  The tall tile reads less per product (a K tile of 64 takes 2.02
+// us against 1.75 for 5/4 of the products) and is taken where it also needs
+// fewer rounds of the chip: M = 9600, N = 4096 is 480 such tiles, 2 rounds,
+// against 608 tiles, 3 rounds (K = 16384: 1035 us, 1.24 PFLOP/s).
+template <int BM_, int BN_>
 struct Shape {
-  static_assert(BN_ == 256 || BN_ == 128, "BN is 256 or 128");
-  static_assert(NWAVES == 8, "8 waves");
-  static constexpr int BM = 256, BN = BN_;
+  static_assert(BN_ == 256 || (BN_ == 128 && BM_ == 256), "256 x 256, 256 x 128 or 320 x 256");
+  static_assert(NWAVES == 8 && (BM_ == 256 || BM_ == 320), "8 waves");
+  static constexpr int BM = BM_, BN = BN_;
   static constexpr int WAVES_M = BN == 128 ? 4 : 2;
   static constexpr int WAVES_N = NWAVES / WAVES_M;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -69,9 +72,10 @@ struct Shape {
   // flight while one is read.  256 x 128 tiles: three of each (48 KB per
   // stage pair); 256 x 256 tiles: two of A and three of B, 32 KB each,
   // which fills the 160 KB (a third B stage: forward GEMM 471 against 478
-  // us, weight gradient 6.69 against 6.76 ms)
+  // us, weight gradient 6.69 against 6.76 ms); 320 x 256 tiles two of each
+  // (144 KB)
   static constexpr int NSA = BN == 128 ? 3 : 2;
-  static constexpr int NSB = 3;
+  static constexpr int NSB = BM == 320 ? 2 : 3;
   static_assert(NSB >= NSA && NSB <= NSA + 1, "the wait below assumes NSA <= NSB <= NSA + 1");
   static constexpr int SMEM = NSA * TA + NSB * TB;
   static_assert(SMEM <= 160 * 1024, "LDS");
@@ -235,11 +239,11 @@ __device__ __forceinline__ void mfma_copies(const Frags<MB, NB>& f, f32x16_t (&a
 
 }  // namespace kk
 
-template <int BN, bool TWO, class Epi, typename E>
+template <int BM_, int BN, bool TWO, class Epi, typename E>
 __global__ void __launch_bounds__(kk::NT, 1)
     gemm_kk(KRows2<E> al, KRows2<E> bl, Epi epi, int M, int N, int K, int ktiles_per_split) {
   using namespace kk;
-  using S = Shape<BN>;
+  using S = Shape<BM_, BN>;
   constexpr int BM = S::BM, MB = S::MB, NB = S::NB, WM = S::WM, WN = S::WN, WAVES_N = S::WAVES_N;
   constexpr int TA = S::TA, TB = S::TB;
   static_assert(sizeof(E) == 2, "bf16 operands only");
@@ -353,19 +357,16 @@ __global__ void __launch_bounds__(kk::NT, 1)
   }
 }
 
-template <int BN = 256, class Epi, typename E>
+template <int BM = 256, int BN = 256, class Epi, typename E>
 inline void launch_gemm_kk(const KRows2<E>& al, const KRows2<E>& bl, const Epi& epi, int M, int N, int K, int splits,
                            hipStream_t s) {
   const int nkt = (K + kk::BK - 1) / kk::BK;
   const int kps = (nkt + splits - 1) / splits;
-  const unsigned tiles = ((M + 255) / 256) * ((N + BN - 1) / BN);
+  const unsigned tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   // operands with a second source (or a row mask) take the two-source copies
-  if (al.p1 != nullptr || bl.p1 != nullptr || al.mask1 != nullptr || bl.mask1 != nullptr)
-    hipLaunchKernelGGL((gemm_kk<BN, true, Epi, E>), dim3(tiles, 1, splits), dim3(kk::NT), 0, s, al, bl, epi, M, N, K,
-                       kps);
-  else
-    hipLaunchKernelGGL((gemm_kk<BN, false, Epi, E>), dim3(tiles, 1, splits), dim3(kk::NT), 0, s, al, bl, epi, M, N, K,
-                       kps);
+  const bool two = al.p1 != nullptr || bl.p1 != nullptr || al.mask1 != nullptr || bl.mask1 != nullptr;
+  auto kernel = two ? gemm_kk<BM, BN, true, Epi, E> : gemm_kk<BM, BN, false, Epi, E>;
+  hipLaunchKernelGGL(kernel, dim3(tiles, 1, splits), dim3(kk::NT), 0, s, al, bl, epi, M, N, K, kps);
 }
 
 // Operands the buffer-load copies can take: K and the source split K0 whole

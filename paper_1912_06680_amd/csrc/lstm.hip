@@ -19,7 +19,7 @@
 //   db    = fixed-order sum of the per-block column sums.
 //
 // Small and middle batches (bf16) and most fp32 shapes take each step, product
-// and cell together, in one launch of lstm_step.h (rules: step_fwd, step_bwd_mf).
+// and cell together, in one launch of lstm_step.h (rules: step_fwd, step_bwd_tile).
 //
 // fp32 path: fp32 matrix products; bf16 path: bf16 ones, with h, the saved
 // gates and dG stored in bf16 and everything else in fp32.
@@ -490,48 +490,54 @@ static inline dim3 transpose_grid(int C, long long rows) {
 // product's with its 256 x 256 (bf16) or 128 x 128 (fp32) tiles, which reuse
 // operands better but need a grid that fills the chip.  us per step, one
 // launch against product and cell, D = H:
-//   bf16  H = 1024: 11.8 / 36 (B = 256), 31.5 / 43 (600: 640 blocks), 46 / 46 (1024)
-//         H = 2048: 33 / 58 (256: 512 blocks), 84 / 87 (600), 138 / 86 (1024)
-//         H = 4096: 44 / 73 (60), 67 / 89 (128: 512 blocks), 137 / 120 (256)
+//   bf16  H = 512: 18 / 27 (B = 600), 19 / 31 (1024: 512 blocks)
+//         H = 1024: 12.5 / 34 (256), 24 / 33 (400), 35 / 34 (600: 640 blocks)
+//         H = 2048: 37 / 43 (256: 512 blocks)
+//         H = 4096: 45 / 72 (60), 69 / 92 (128: 512 blocks)
 //   fp32  H = 512: 44 / 57 (B = 1024), 179 / 164 (4096: 512 tiles)
 //         H = 1024: 43 / 65 (256), 300 / 302 (2048: 512 tiles)
 static bool step_fwd(o5_dtype dt, int B, int D, int H) {
   if (!step::offsets_fit(dtype_size(dt), B, D, H)) return false;
   if (dt == O5_F32) return static_cast<long long>(cdiv(B, 128)) * cdiv(4 * H, 128) < 512;
-  return static_cast<long long>(cdiv(B, 64)) * (H / step::UNITS) <= 768;
+  return static_cast<long long>(cdiv(B, 64)) * (H / step::UNITS) <= 512;
 }
 
-// Tile of the backward step's launch of lstm_step.h (16 MF rows x 16 MF
-// units), or 0 where the product (split over K) and the cell are launches of
+// Tile (rows and units) of the backward step's launch of lstm_step.h, or 0 where the product (split over K) and the cell are launches of
 // their own.  Whole calls of 16 steps in us, one launch per step against two:
-//   bf16  H = 1024: 296 / 443 (B = 256: 256 blocks of 32 x 32), 854 / 709 (600)
-//         H = 2048: 463 / 651 (128), 823 / 818 (256: 512 blocks)
-//         H = 4096: 863 / 1190 (60), 1436 / 1454 (128: 512 blocks)
+//   bf16  H = 512: 221 / 292 (B = 256), 419 / 406 (600: 304 blocks of 32 x 32)
+//         H = 1024: 284 / 382 (256: 256 blocks), 544 / 490 (400)
+//         H = 2048: 458 / 517 (128: 256 blocks), 759 / 622 (192)
+//         H = 4096: 866 / 956 (60: 256 blocks), 1430 / 1185 (96)
+// (a second round of blocks costs as much as the first).
 //   fp32  H = 512: 296 / 242 (B = 60: 32 blocks, each with the whole K)
 //         H = 2048: 1259 / 1100 (60), 3680 / 3848 (256)
 //         H = 4096: 3581 / 3836 (60: 256 blocks), 13367 / 15008 (256)
 // In fp32 a few blocks each walk all of K on the matrix units, so the grid has
 // to fill the chip unless K is short; 64 x 64 tiles take 0.9 of the time of
 // four 32 x 32 ones, so the fewer rounds of the chip decide.
-static int step_bwd_mf(o5_dtype dt, int B, int D, int H) {
+static int step_bwd_tile(o5_dtype dt, int B, int D, int H) {
   if (!step::offsets_fit(dtype_size(dt), B, D, H)) return 0;
   const long long n2 = static_cast<long long>(cdiv(B, 32)) * (H / 32);
-  if (dt == O5_BF16) return n2 <= 384 ? 2 : 0;
+  if (dt == O5_BF16) return n2 <= 256 ? 32 : 0;
   if (n2 < 256 && H > 256) return 0;
   const long long n4 = static_cast<long long>(cdiv(B, 64)) * (H / 64);
-  return n4 >= 256 && 3.6 * static_cast<double>((n4 + 255) / 256) < static_cast<double>((n2 + 255) / 256) ? 4 : 2;
+  return n4 >= 256 && 3.6 * static_cast<double>((n4 + 255) / 256) < static_cast<double>((n2 + 255) / 256) ? 64 : 32;
 }
 
 struct FwdWs {
   size_t pre, h0e, total;
-  bool step;
+  bool step, fused;
   GemmPlan plan;
 };
 
 static FwdWs fwd_ws(o5_dtype dt, int T, int B, int D, int H) {
   (void)T;
   FwdWs w;
-  w.plan = plan_gemm(dt == O5_BF16, B, 4 * H, D + H);
+  // (one split of a big enough grid: the cell runs in the product's epilogue,
+  // on 256 x 256 tiles)
+  w.fused = dt == O5_BF16 && k_splits(B, 4 * H, D + H) == 1 &&
+            static_cast<long long>(cdiv(B, 256)) * cdiv(4 * H, 256) >= 64;
+  w.plan = plan_gemm(dt == O5_BF16, B, 4 * H, D + H, Split::kStep);
   w.step = step_fwd(dt, B, D, H);
   size_t o = 0;
   w.pre = o;
@@ -545,31 +551,33 @@ static FwdWs fwd_ws(o5_dtype dt, int T, int B, int D, int H) {
 struct BwdWs {
   size_t dG, dc, rec, h0e, dbpart, dGT, XHT, WhT, total;
   int nbc;
-  int step_mf;  // tile of the one-launch backward step, or 0
+  int step_tile;  // tile of the one-launch backward step, or 0
   int Bp;       // B rounded up to the cell's row block (bf16 path: time-padded K of dW)
   size_t ldt;   // T * Bp, the leading dimension of dGT and XHT
   GemmPlan plan_dh, plan_dw, plan_dx;
 };
 
-static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H) {
+static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H, bool fact) {
   BwdWs w;
   const bool bf = dt == O5_BF16;
   w.Bp = time_pad(B);
   w.nbc = w.Bp / kPwRows;  // cell row blocks; those past B only write zeros
   w.ldt = static_cast<size_t>(T) * w.Bp;
-  w.plan_dh = plan_gemm(bf, B, H, 4 * H);
-  w.plan_dw = plan_gemm(bf, 4 * H, D + H, bf ? static_cast<int>(w.ldt) : T * B);
-  w.plan_dw.splits = 1;  // dW is written directly (M x N tiles are plentiful)
-  w.plan_dx = plan_gemm(bf, T * B, D, 4 * H);
-  w.plan_dx.splits = 1;
+  // (the workspace query serves both backward calls: partial sums for the
+  // larger split of the two)
+  w.plan_dh = plan_gemm(bf, B, H, 4 * H, fact ? Split::kStep : Split::kFree);
+  const int most = std::max(plan_gemm(bf, B, H, 4 * H, Split::kStep).splits, plan_gemm(bf, B, H, 4 * H, Split::kFree).splits);
+  // dW and dx are written directly (M x N tiles are plentiful)
+  w.plan_dw = plan_gemm(bf, 4 * H, D + H, bf ? static_cast<int>(w.ldt) : T * B, Split::kOne);
+  w.plan_dx = plan_gemm(bf, T * B, D, 4 * H, Split::kOne);
   size_t o = 0;
   w.dG = o;
   o += align_up(static_cast<size_t>(T) * B * 4 * H * dtype_size(dt));
   w.dc = o;
   o += align_up(static_cast<size_t>(B) * H * sizeof(float));
   w.rec = o;
-  w.step_mf = step_bwd_mf(dt, B, D, H);
-  if (w.step_mf == 0) o += align_up(static_cast<size_t>(w.plan_dh.splits) * B * H * sizeof(float));
+  w.step_tile = step_bwd_tile(dt, B, D, H);
+  if (w.step_tile == 0) o += align_up(static_cast<size_t>(most) * B * H * sizeof(float));
   w.h0e = o;
   o += align_up(static_cast<size_t>(B) * H * dtype_size(dt));
   w.dbpart = o;
@@ -580,10 +588,11 @@ static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H) {
     w.dGT = o;
     o += align_up(static_cast<size_t>(4) * H * w.ldt * sizeof(uint16_t));
     w.XHT = o;
-    o += align_up(static_cast<size_t>(D + H) * w.ldt * sizeof(uint16_t));
+    // (W_x^T [D][4H] of the input gradient takes its place afterwards)
+    o += align_up(std::max(static_cast<size_t>(D + H) * w.ldt, static_cast<size_t>(D) * 4 * H) * sizeof(uint16_t));
     w.WhT = o;
     o += align_up(static_cast<size_t>(H) * 4 * H * sizeof(uint16_t));
-  } else if (w.step_mf != 0) {
+  } else if (w.step_tile != 0) {
     o += align_up(static_cast<size_t>(H) * 4 * H * sizeof(float));  // W_h^T
   }
   w.total = o;
@@ -627,7 +636,8 @@ static int lstm_fwd_impl(int T, int B, int D, int H, const E* x, const E* Wx, co
     // small and middle batches, and fp32: one launch per step, no partial sums
     for (int t = 0; t < T; ++t) {
       ktimer_begin(kSiteLstmFwdGemm, s);
-      launch_step_fwd(B, D, H, x + static_cast<size_t>(t) * B * D, t == 0 ? h0e : h + (t - 1) * BH, Wx, Wh, bias,
+      const int S = sizeof(E) == 2 ? w.plan.splits : 0;
+      launch_step_fwd(B, D, H, S, S ? cdiv((D + H) / 64, S) : 0, x + static_cast<size_t>(t) * B * D, t == 0 ? h0e : h + (t - 1) * BH, Wx, Wh, bias,
                       t == 0 ? c0 : c + (t - 1) * BH, reset ? reset + static_cast<size_t>(t) * B : nullptr, h + t * BH,
                       c + t * BH, gates ? gates + static_cast<size_t>(t) * B * 4 * H : nullptr, s);
       ktimer_end(kSiteLstmFwdGemm, s);
@@ -635,7 +645,7 @@ static int lstm_fwd_impl(int T, int B, int D, int H, const E* x, const E* Wx, co
     return check_launch("o5_lstm_fwd");
   }
   if constexpr (sizeof(E) == 2) {
-    if (w.plan.tile == BfTile::kDma256 && w.plan.splits == 1) {
+    if (w.fused) {
       // one launch per step: GEMM with the cell fused into its epilogue
       for (int t = 0; t < T; ++t) {
         const E* hprev = t == 0 ? h0e : h + (t - 1) * BH;
@@ -695,7 +705,7 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
   float* dbpart = reinterpret_cast<float*>(ws + w.dbpart);
   E* dGT = kBf ? reinterpret_cast<E*>(ws + w.dGT) : nullptr;
   E* XHT = kBf ? reinterpret_cast<E*>(ws + w.XHT) : nullptr;
-  E* WhT = kBf || w.step_mf != 0 ? reinterpret_cast<E*>(ws + w.WhT) : nullptr;
+  E* WhT = kBf || w.step_tile != 0 ? reinterpret_cast<E*>(ws + w.WhT) : nullptr;
   const E* h0e;
   if constexpr (kBf) {
     E* tmp = reinterpret_cast<E*>(ws + w.h0e);
@@ -707,7 +717,7 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
                        Wh, 4 * H, H, nullptr, WhT, static_cast<size_t>(4 * H));
   } else {
     h0e = h0;
-    if (w.step_mf != 0)
+    if (w.step_tile != 0)
       hipLaunchKernelGGL(transpose_f32, dim3(H / 64, 4 * H / 64), dim3(256), 0, s, 4 * H, H, Wh, WhT);
   }
   const dim3 pw_grid(cdiv(H, kPwCols), w.nbc);
@@ -716,15 +726,20 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
               : w.plan_dh.splits <= 8 ? lstm_bwd_cell<E, 8>
                                       : lstm_bwd_cell<E, 16>;
   const bool fact = P != nullptr;
-  for (int t = T - 1; t >= 0 && w.step_mf != 0; --t) {
+  for (int t = T - 1; t >= 0 && w.step_tile != 0; --t) {
     // small and middle batches, and fp32: one launch per step
     const bool last = t == T - 1;
     ktimer_begin(kSiteLstmBwdCell, s);
-    const int rows = 16 * w.step_mf;
-    auto kernel = step::lstm_step_bwd<E, 2, 2>;
+    const int rows = w.step_tile;
+    auto kernel = step::lstm_step_bwd<E, 32>;
     if constexpr (!kBf)
-      if (w.step_mf == 4) kernel = step::lstm_step_bwd<E, 4, 4>;
-    hipLaunchKernelGGL(kernel, dim3((w.Bp / rows) * (H / rows)), dim3(step::NT), 0, s, B, w.Bp, H,
+      if (rows == 64) kernel = step::lstm_step_bwd<E, 64>;
+    // the partial sums: the factored call's as its separate product would
+    // take them (one over P alone at the last step), else one per wave
+    const int nk = ((fact ? ldp : 0) + (last ? 0 : 4 * H)) / 64;
+    const int S = !kBf ? 0 : !fact ? step::NW : last ? 1 : w.plan_dh.splits;
+    hipLaunchKernelGGL(kernel, dim3((w.Bp / rows) * (H / rows)), dim3(step::NT), 0, s, B, w.Bp, H, S,
+                       S ? cdiv(nk, S) : 0,
                        fact ? P + static_cast<size_t>(t) * B * ldp : nullptr, Wf, fact ? ldp : 0,
                        last ? nullptr : dG + (t + 1) * BG, WhT,
                        reset && !last ? reset + static_cast<size_t>(t + 1) * B : nullptr,
@@ -733,7 +748,7 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
                        dG + t * BG, dbpart, last ? 0 : 1, dGT, w.ldt, t * w.Bp);
     ktimer_end(kSiteLstmBwdCell, s);
   }
-  for (int t = T - 1; t >= 0 && w.step_mf == 0; --t) {
+  for (int t = T - 1; t >= 0 && w.step_tile == 0; --t) {
     const float* recp = nullptr;
     int S = w.plan_dh.splits;  // partial sums the cell adds
     if (fact) {
@@ -813,10 +828,22 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
     // dx = dG . W_x :  A(i=r, k=n) = dG[r, n];  B(j=d, k=n) = W_x[n, d]
     const int R = T * B;
     KRows2<E> al{dG, nullptr, nullptr, 4 * H, 0, 4 * H, 4 * H, R};
-    ICols2<E> bl{Wx, nullptr, nullptr, nullptr, D, 0, D, D, 4 * H, 0};
     EpiStoreElem<E> epi{dx, D};
     ktimer_begin(kSiteLstmDxGemm, s);
-    run_gemm(w.plan_dx, al, bl, epi, R, D, 4 * H, s);
+    if constexpr (kBf) {
+      // W_x^T [D][4H] takes the place of [x | h~]^T, which the weight
+      // gradient was the last to read: with both operands K-contiguous the
+      // product runs on gemm_kk (T B = 9600, D = H = 4096: 1035 + 47 us with
+      // the transposition against 1784 us on an I-contiguous W_x)
+      E* WxT = XHT;
+      hipLaunchKernelGGL(transpose_rows<E>, transpose_grid(D, 4 * H), dim3(256), 0, s, 1, 4 * H, 4 * H, D, Wx, Wx,
+                         4 * H, D, nullptr, WxT, static_cast<size_t>(4 * H));
+      KRows2<E> bl{WxT, nullptr, nullptr, 4 * H, 0, 4 * H, 4 * H, D};
+      run_gemm(w.plan_dx, al, bl, epi, R, D, 4 * H, s);
+    } else {
+      ICols2<E> bl{Wx, nullptr, nullptr, nullptr, D, 0, D, D, 4 * H, 0};
+      run_gemm(w.plan_dx, al, bl, epi, R, D, 4 * H, s);
+    }
     ktimer_end(kSiteLstmDxGemm, s);
   }
   return check_launch("o5_lstm_bptt");
@@ -867,14 +894,14 @@ extern "C" int o5_lstm_fwd(o5_dtype dt, int T, int B, int D, int H, const void* 
 
 extern "C" size_t o5_lstm_bptt_workspace_bytes(o5_dtype dt, int T, int B, int D, int H) {
   if (check_dims("o5_lstm_bptt_workspace_bytes", dt, T, B, D, H) != O5_OK) return 0;
-  return bwd_ws(dt, T, B, D, H).total;
+  return bwd_ws(dt, T, B, D, H, false).total;
 }
 
 // Validation shared by the two backward calls (all but the heads' gradient).
 static int bptt_check(const char* fn, o5_dtype dt, int T, int B, int D, int H, const void* x, const void* Wx,
                       const void* Wh, const float* h0, const float* c0, const uint8_t* reset, const void* h,
                       const float* c, const void* gates, const float* dhT, const float* dcT, float* dWx, float* dWh,
-                      float* db, void* dx, void* ws, size_t ws_bytes, BwdWs* w) {
+                      float* db, void* dx, void* ws, size_t ws_bytes, bool fact, BwdWs* w) {
   int st = check_dims(fn, dt, T, B, D, H);
   if (st != O5_OK) return st;
   O5_PTR_IN(fn, x, "x");
@@ -892,7 +919,7 @@ static int bptt_check(const char* fn, o5_dtype dt, int T, int B, int D, int H, c
   O5_PTR_IN(fn, dWh, "dWh");
   O5_PTR_IN(fn, db, "db");
   O5_OPT_PTR_IN(fn, dx, "dx");
-  *w = bwd_ws(dt, T, B, D, H);
+  *w = bwd_ws(dt, T, B, D, H, fact);
   O5_CHECK(ws != nullptr && ws_bytes >= w->total, O5_E_WORKSPACE, "%s: workspace needs %zu bytes, got %zu", fn,
            w->total, ws ? ws_bytes : static_cast<size_t>(0));
   O5_CHECK(aligned16(ws), O5_E_ALIGN, "%s: ws is not 16-byte aligned", fn);
@@ -905,7 +932,7 @@ extern "C" int o5_lstm_bptt(o5_dtype dt, int T, int B, int D, int H, const void*
                             float* dWh, float* db, void* dx, void* ws, size_t ws_bytes, void* stream) {
   BwdWs w;
   const int st = bptt_check("o5_lstm_bptt", dt, T, B, D, H, x, Wx, Wh, h0, c0, reset, h, c, gates, dhT, dcT, dWx,
-                            dWh, db, dx, ws, ws_bytes, &w);
+                            dWh, db, dx, ws, ws_bytes, false, &w);
   if (st != O5_OK) return st;
   O5_PTR(dh, "dh");
   char* wsp = static_cast<char*>(ws);
@@ -930,7 +957,7 @@ extern "C" int o5_lstm_bptt_factored(o5_dtype dt, int T, int B, int D, int H, co
            static_cast<int>(dt));
   BwdWs w;
   const int st = bptt_check("o5_lstm_bptt_factored", dt, T, B, D, H, x, Wx, Wh, h0, c0, reset, h, c, gates, dhT,
-                            dcT, dWx, dWh, db, dx, ws, ws_bytes, &w);
+                            dcT, dWx, dWh, db, dx, ws, ws_bytes, true, &w);
   if (st != O5_OK) return st;
   O5_CHECK(ld >= 64 && ld % 64 == 0 && ld <= 4096, O5_E_SHAPE,
            "o5_lstm_bptt_factored: ld=%d must be a multiple of 64 in 64..4096", ld);

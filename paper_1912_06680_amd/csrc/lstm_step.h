@@ -5,20 +5,22 @@
 //   backward  R = [P_t | dG_{t+1}] . [W | W_h^T]^T, then the gate gradients
 //             (P, W only where the heads' gradient comes in factored form)
 //
-// A block owns 16 MF batch rows x 16 hidden units (forward: their four gates,
-// 64 columns) or 16 MF rows x 16 NF units (backward) for the whole reduction,
+// A block owns 16 to 64 batch rows x 16 hidden units (forward: their four
+// gates, 64 columns) or T x T rows and units (backward) for the whole reduction,
 // so no partial sum goes through HBM and the cell needs no second launch.
-// Its 4 waves split K: wave w takes the 128-byte pieces w, w + 4, ... of
-// every row, so the block reads 512 bytes of each row at a time.  A wave copies
+// Its 4 waves split K into 128-byte pieces of every row.  A wave copies
 // its pieces straight to LDS (buffer loads, 8 rows x 128 bytes each: whole
 // cache lines, four consecutive lanes in one) into a ring of its own, so the
-// loop has no barrier; it reads the MFMA fragments (v_mfma_f32_16x16x32_bf16,
-// or v_mfma_f32_16x16x4_f32) and refills the stage before it multiplies.  The
-// 4 partial tiles meet once in LDS, are added in wave order, and the same
-// threads finish the cell.  (Fragments loaded from memory straight into
+// loop has no barrier; it reads the MFMA fragments (v_mfma_f32_32x32x16_bf16,
+// or v_mfma_f32_16x16x4_f32) and refills the stage while it multiplies.  The
+// partial tiles meet once in LDS, are added in order, and the same threads
+// finish the cell.  In bf16 the K ranges of the partial sums and the order
+// within them are those of the separate product (gemm_plan.h), so a shape's
+// results do not depend on which of the two paths serves it; in fp32 wave w
+// takes pieces w, w + 4, ....  (Fragments loaded from memory straight into
 // registers, 16 rows x 64 bytes with consecutive lanes on different rows,
 // took 22.8 us for a bf16 step of B = 256, D = H = 1024;
-// this form takes 11.7, the product and cell as two launches took 36.)
+// this form takes 12.5, the product and cell as two launches took 36.)
 //
 // Tiles are dealt so that an XCD holds all row blocks of a run of units: its
 // share of the weights is read into its L2 once per step.
@@ -33,35 +35,54 @@ namespace step {
 constexpr int NW = 4;
 constexpr int NT = NW * 64;
 constexpr int PIECE = 128;          // bytes of a row per piece: a cache line
-constexpr int HALVES = PIECE / 64;  // MFMA k steps per piece
 constexpr int CPR = PIECE / 16;     // 16-byte chunks per stage row
 constexpr int RPC = 1024 / PIECE;   // rows per copy
 constexpr int UNITS = 16;           // hidden units per block (forward)
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void mma(const uint4& a, const uint4& b, f4_t& c, const uint16_t*) {
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0,
-                                              0);
-}
-__device__ __forceinline__ void mma(const uint4& a, const uint4& b, f4_t& c, const float*) {
-  const f4_t x = __builtin_bit_cast(f4_t, a), y = __builtin_bit_cast(f4_t, b);
+// The fragments of a type: R rows (or columns) per block of the accumulator,
+// STEPS 16-byte reads per lane and piece, and where an accumulator element
+// lies (lane -> column, lane and element -> row).
+template <typename E>
+struct Frag;
+template <>
+struct Frag<uint16_t> {  // 32 x 32 x 16: two chunks per step, one per half wave
+  static constexpr int R = 32, STEPS = 4, N = 16;
+  typedef f32x16_t acc_t;
+  __device__ __forceinline__ static int chunk(int s, int lane) { return 2 * s + (lane >> 5); }
+  __device__ __forceinline__ static int row(int e, int lane) { return 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); }
+  __device__ __forceinline__ static void mma(const uint4& a, const uint4& b, acc_t& c) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0,
+                                                0, 0);
+  }
+};
+template <>
+struct Frag<float> {  // 16 x 16 x 4, four times: four chunks per step, one per quarter wave
+  static constexpr int R = 16, STEPS = 2, N = 4;
+  typedef f4_t acc_t;
+  __device__ __forceinline__ static int chunk(int s, int lane) { return 4 * s + (lane >> 4); }
+  __device__ __forceinline__ static int row(int e, int lane) { return 4 * (lane >> 4) + e; }
+  __device__ __forceinline__ static void mma(const uint4& a, const uint4& b, acc_t& c) {
+    const f4_t x = __builtin_bit_cast(f4_t, a), y = __builtin_bit_cast(f4_t, b);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], y[q], c, 0, 0, 0);
-}
+    for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], y[q], c, 0, 0, 0);
+  }
+};
 
-// 16-byte chunk c of stage row r is stored at slot c ^ (r / (256 / PIECE)) %
-// CPR: the 16 rows of a fragment read fall on 16 distinct 16-byte bank groups.
-__device__ __forceinline__ int slot(int r, int c) { return c ^ ((r / (256 / PIECE)) % CPR); }
+// 16-byte chunk c of stage row r is stored at slot c ^ (r / 2) % 8: 16 rows
+// read at one chunk fall on 16 distinct 16-byte bank groups.
+__device__ __forceinline__ int slot(int r, int c) { return c ^ ((r >> 1) & 7); }
 
-// One operand of F 16-row fragments with two sources along K: source 0 holds
+// One operand of ROWS stage rows with two sources along K: source 0 holds
 // pieces [0, n0), source 1 the rest up to n.  A lane's byte offset into each
 // source is fixed (copy q of a piece moves stage rows 8 q .. 8 q + 7); a row
 // that reads zeros has an offset past the buffer.
-template <int F>
+template <int ROWS>
 struct Operand {
+  static constexpr int COPIES = ROWS / RPC;
   kk::rsrc_t r0, r1;
-  uint32_t v0[HALVES * F], v1[HALVES * F];
+  uint32_t v0[COPIES], v1[COPIES];
   int n0, n;
 
   // rows [0, rows) of ld0 / ld1 bytes; row(r) gives the source row of stage
@@ -74,7 +95,7 @@ struct Operand {
     r0 = kk::make_rsrc(p0, rows * ld0);
     r1 = kk::make_rsrc(p1, rows * ld1);
 #pragma unroll
-    for (int q = 0; q < HALVES * F; ++q) {
+    for (int q = 0; q < COPIES; ++q) {
       const int r = RPC * q + lane / CPR;
       const uint32_t c = slot(r, lane % CPR) * 16;
       bool masked = false;
@@ -83,131 +104,188 @@ struct Operand {
       v1[q] = sr < rows && !masked ? sr * ld1 + c : kk::kOutOfRange;
     }
   }
-  // copy q of piece u, to the stage at LDS address `lds` (past the last
-  // piece: zeros, nothing read)
+  // copy q of piece u, to the stage at LDS address `lds` (no such piece:
+  // zeros, nothing read)
   __device__ __forceinline__ void issue_one(int u, uint32_t lds, int q) const {
-    const bool s0 = u < n0;
+    const bool none = u < 0 || u >= n;
+    const bool s0 = none || u < n0;
     kk::rsrc_t rs = s0 ? r0 : r1;
-    if (u >= n) rs.z = 0;
-    const uint32_t soff = static_cast<uint32_t>(s0 ? u : u - n0) * PIECE;
+    if (none) rs.z = 0;  // an empty buffer: every offset reads zero
+    const uint32_t soff = none ? 0u : static_cast<uint32_t>(s0 ? u : u - n0) * PIECE;
     asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(s0 ? v0[q] : v1[q]),
                  "s"(rs), "s"(soff), "s"(lds + q * 1024)
                  : "memory", "m0");
   }
-  // fragment f, half q (64 bytes) of the piece in `stage`
-  __device__ __forceinline__ static uint4 read(const char* stage, int f, int q, int lane) {
-    const int r = 16 * f + (lane & 15);
-    return *reinterpret_cast<const uint4*>(stage + r * PIECE + slot(r, q * 4 + (lane >> 4)) * 16);
+};
+
+// Fragment f, step s of the piece in `stage`.
+template <typename E>
+__device__ __forceinline__ uint4 read_frag(const char* stage, int f, int s, int lane) {
+  const int r = Frag<E>::R * f + (lane & (Frag<E>::R - 1));
+  return *reinterpret_cast<const uint4*>(stage + r * PIECE + slot(r, Frag<E>::chunk(s, lane)) * 16);
+}
+
+// The pieces of one wave: up to two runs (each a partial sum of its own), run
+// q the cnt[q] pieces first[q], first[q] + stride, ....
+struct Runs {
+  int first[2], cnt[2], stride;
+  // piece i of the wave, run 0 padded to an even count; -1: zeros
+  __device__ __forceinline__ int at(int i) const {
+    const int pad = (cnt[0] + 1) & ~1;
+    const int q = i < pad ? 0 : 1;
+    const int k = i - (q ? pad : 0);
+    return k < cnt[q] ? first[q] + k * stride : -1;
   }
 };
 
-// LDS bytes of the rings of the waves.
-template <int NA, int NB, int NST>
-constexpr size_t ring_bytes() {
-  return static_cast<size_t>(NW) * NST * (NA + NB) * 16 * PIECE;
+// The K ranges of a wave: S partial sums of kps pieces each, the wave's own
+// first and, beyond NW, its second; S = 0: one run of every NW-th piece.
+__device__ __forceinline__ Runs runs_of(int S, int kps, int n, int wave) {
+  Runs r;
+  if (S == 0) {
+    r.stride = NW;
+    r.first[0] = wave;
+    r.cnt[0] = max(0, (n - wave + NW - 1) / NW);
+    r.first[1] = r.cnt[1] = 0;
+  } else {
+    r.stride = 1;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int sp = wave + q * NW;
+      r.first[q] = sp * kps;
+      r.cnt[q] = sp < S ? max(0, min(n, (sp + 1) * kps) - sp * kps) : 0;
+    }
+  }
+  return r;
 }
 
-// acc[a][b] += this wave's pieces of the NA x NB fragments' product, through
-// NST stages of the wave's own.  While the products of piece i run from
-// registers, piece i + NST is copied into the stage that piece i was read out
-// of (the first half of the products) and the fragments of piece i + 1 are
-// read (the second half); scheduling barriers keep one copy or read between
-// products, so a wave alone on its SIMD overlaps the three (31.6 against 33.1
-// us one after the other for B = 256, D = H = 2048 in bf16).  Measured
-// slower: pieces of 64 bytes in twice the stages (half lines: 40 us), two
-// waves with twice the stages each (44 us).
-template <typename E, int NST, int NA, int NB>
-__device__ __forceinline__ void k_loop(const Operand<NA>& oa, const Operand<NB>& ob, char* smem, int wave, int lane,
-                                       f4_t (&acc)[NA][NB]) {
-  constexpr int STAGE = (NA + NB) * 16 * PIECE;
-  constexpr int COPIES = HALVES * (NA + NB);  // per stage; also the fragment reads per piece
-  constexpr int MM = HALVES * NA * NB;        // products per piece (of one k step each)
-  static_assert(MM % 2 == 0, "halves of a piece's products");
+// acc[q][a][b] = the products of the wave's run q, through NST stages of the
+// wave's own.  While the products of piece i run from registers, piece i +
+// NST is copied into the stage that piece i was read out of (the first half
+// of the products) and the fragments of piece i + 1 are read (the second
+// half); scheduling barriers keep one copy or read between products, so a
+// wave alone on its SIMD overlaps the three (31.6 against 33.1 us one after
+// the other for B = 256, D = H = 2048 in bf16).  Measured slower: pieces of 64
+// bytes in twice the stages (half lines: 40 us), two waves with twice the
+// stages each (44 us).
+template <typename E, int NST, int RA, int RB, int Q>
+__device__ __forceinline__ void k_loop(const Operand<RA>& oa, const Operand<RB>& ob, const Runs& runs, char* smem,
+                                       int wave, int lane,
+                                       typename Frag<E>::acc_t (&acc)[Q][RA / Frag<E>::R][RB / Frag<E>::R]) {
+  typedef Frag<E> F;
+  constexpr int NA = RA / F::R, NB = RB / F::R;
+  constexpr int STAGE = (RA + RB) * PIECE;
+  constexpr int COPIES = Operand<RA>::COPIES + Operand<RB>::COPIES;  // per stage
+  constexpr int READS = F::STEPS * (NA + NB);                        // per piece
+  constexpr int HALF = F::STEPS * NA * NB / 2;                       // products per half piece
   char* mine = smem + wave * NST * STAGE;
   const uint32_t l0 = static_cast<uint32_t>(reinterpret_cast<size_t>((__attribute__((address_space(3))) char*)mine));
-  const int cnt = (oa.n - wave + NW - 1) / NW;  // this wave's pieces (may be <= 0)
-  uint4 fa[2][HALVES][NA], fb[2][HALVES][NB];
-  auto issue_one = [&](int i, int st, int c) {
-    if (c < HALVES * NA)
-      oa.issue_one(wave + i * NW, l0 + st, c);
+  uint4 fa[2][F::STEPS][NA], fb[2][F::STEPS][NB];
+  auto issue_one = [&](int u, int st, int c) {
+    if (c < Operand<RA>::COPIES)
+      oa.issue_one(u, l0 + st, c);
     else
-      ob.issue_one(wave + i * NW, l0 + st + NA * 16 * PIECE, c - HALVES * NA);
+      ob.issue_one(u, l0 + st + RA * PIECE, c - Operand<RA>::COPIES);
   };
-  // read c of a piece's fragments: those of k step 0 first
+  // read c of a piece's fragments: those of step 0 first
   auto read_one = [&](const char* st, int f, int c) {
-    const int q = c / (NA + NB), k = c % (NA + NB);
+    const int s = c / (NA + NB), k = c % (NA + NB);
     if (k < NB)
-      fb[f][q][k] = Operand<NB>::read(st + NA * 16 * PIECE, k, q, lane);
+      fb[f][s][k] = read_frag<E>(st + RA * PIECE, k, s, lane);
     else
-      fa[f][q][k - NB] = Operand<NA>::read(st, k - NB, q, lane);
+      fa[f][s][k - NB] = read_frag<E>(st, k - NB, s, lane);
   };
-  auto product = [&](int f, int m) {
-    const int q = m / (NA * NB), a = m / NB % NA, b = m % NB;
-    mma(fa[f][q][a], fb[f][q][b], acc[a][b], static_cast<const E*>(nullptr));
-  };
-  if (cnt <= 0) return;
+  const int total = ((runs.cnt[0] + 1) & ~1) + runs.cnt[1];
+  if (total <= 0) return;
 #pragma unroll
-  for (int s = 0; s < NST; ++s)
+  for (int s = 0; s < NST; ++s) {
+    const int u = runs.at(s);
 #pragma unroll
-    for (int c = 0; c < COPIES; ++c) issue_one(s, s * STAGE, c);
+    for (int c = 0; c < COPIES; ++c) issue_one(u, s * STAGE, c);
+  }
   dma::vm_wait<(NST - 1) * COPIES>();
 #pragma unroll
-  for (int c = 0; c < COPIES; ++c) read_one(mine, 0, c);
+  for (int c = 0; c < READS; ++c) read_one(mine, 0, c);
   int st = 0;  // byte offset of piece i's stage
-  auto step = [&](int i, auto F) {
-    constexpr int f = decltype(F)::value;
-    const int nx = st + STAGE == NST * STAGE ? 0 : st + STAGE;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // piece i is read out: its stage is free
-    __builtin_amdgcn_sched_barrier(0);
-    dma::unroll<0, MM / 2>([&](auto M) {
-      constexpr int m = decltype(M)::value;
-      product(f, m);
-      dma::unroll<m * COPIES / (MM / 2), (m + 1) * COPIES / (MM / 2)>(
-          [&](auto C) { issue_one(i + NST, st, decltype(C)::value); });
+  dma::unroll<0, Q>([&](auto QI) {
+    constexpr int q = decltype(QI)::value;
+    auto product = [&](int f, int m) {
+      const int s = m / (NA * NB), a = m / NB % NA, b = m % NB;
+      F::mma(fa[f][s][a], fb[f][s][b], acc[q][a][b]);
+    };
+    auto step = [&](int i, auto FI) {
+      constexpr int f = decltype(FI)::value;
+      const int nx = st + STAGE == NST * STAGE ? 0 : st + STAGE;
+      const int u = runs.at(i + NST);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // piece i is read out: its stage is free
       __builtin_amdgcn_sched_barrier(0);
-    });
-    dma::vm_wait<(NST - 1) * COPIES>();  // piece i + 1 has landed
-    const char* np = mine + nx;
-    dma::unroll<0, MM / 2>([&](auto M) {
-      constexpr int m = decltype(M)::value;
-      product(f, MM / 2 + m);
-      dma::unroll<m * COPIES / (MM / 2), (m + 1) * COPIES / (MM / 2)>(
-          [&](auto C) { read_one(np, f ^ 1, decltype(C)::value); });
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    st = nx;
-  };
-  // (an odd count takes one piece of zeros more: a tail of its own would cost
-  // accumulator moves in every iteration)
-  for (int i = 0; i < cnt; i += 2) {
-    step(i, std::integral_constant<int, 0>{});
-    step(i + 1, std::integral_constant<int, 1>{});
-  }
+      dma::unroll<0, HALF>([&](auto M) {
+        constexpr int m = decltype(M)::value;
+        product(f, m);
+        dma::unroll<m * COPIES / HALF, (m + 1) * COPIES / HALF>([&](auto C) { issue_one(u, st, decltype(C)::value); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      dma::vm_wait<(NST - 1) * COPIES>();  // piece i + 1 has landed
+      const char* np = mine + nx;
+      dma::unroll<0, HALF>([&](auto M) {
+        constexpr int m = decltype(M)::value;
+        product(f, HALF + m);
+        dma::unroll<m * READS / HALF, (m + 1) * READS / HALF>([&](auto C) { read_one(np, f ^ 1, decltype(C)::value); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      st = nx;
+    };
+    // (an odd count takes one piece of zeros more: a tail of its own would
+    // cost accumulator moves in every iteration)
+    const int i0 = q == 0 ? 0 : (runs.cnt[0] + 1) & ~1;
+    for (int i = i0; i < i0 + runs.cnt[q]; i += 2) {
+      step(i, std::integral_constant<int, 0>{});
+      step(i + 1, std::integral_constant<int, 1>{});
+    }
+  });
   dma::vm_wait<0>();  // no copy outlives the loop
 }
 
-// Leaves the wave's accumulators in red [NW][16 NA][PITCH] (fragment layout:
-// lane holds column lane % 16, element e row 4 (lane / 16) + e).
-template <int NA, int NB, int PITCH>
-__device__ __forceinline__ void park(const f4_t (&acc)[NA][NB], float* red, int wave, int lane) {
+template <typename A, int Q, int NA, int NB>
+__device__ __forceinline__ void zero_acc(A (&acc)[Q][NA][NB]) {
 #pragma unroll
-  for (int a = 0; a < NA; ++a)
+  for (int q = 0; q < Q; ++q)
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        red[(wave * 16 * NA + 16 * a + 4 * (lane >> 4) + e) * PITCH + 16 * b + (lane & 15)] = acc[a][b][e];
+      for (int b = 0; b < NB; ++b) acc[q][a][b] = A{};
 }
 
-// The waves' partial sums of (row, col), in wave order.
-template <int ROWS, int PITCH>
-__device__ __forceinline__ float gather(const float* red, int row, int col) {
-  float v[NW];
+// Leaves the accumulators of the wave's runs below S in red [S][RA][PITCH].
+template <typename E, int RA, int PITCH, int Q, int NA, int NB>
+__device__ __forceinline__ void park(const typename Frag<E>::acc_t (&acc)[Q][NA][NB], float* red, int S, int wave,
+                                     int lane) {
+  typedef Frag<E> F;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) v[w] = red[(w * ROWS + row) * PITCH + col];
-  float s = v[0];
+  for (int q = 0; q < Q; ++q) {
+    const int sp = wave + q * NW;
+    if (sp >= S) continue;
 #pragma unroll
-  for (int w = 1; w < NW; ++w) s += v[w];
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < F::N; ++e) {
+          const int row = F::R * a + F::row(e, lane);
+          if (row < RA) red[(sp * RA + row) * PITCH + F::R * b + (lane & (F::R - 1))] = acc[q][a][b][e];
+        }
+  }
+}
+
+// s + the first S of the MAXS partial sums of (row, col), in order (all are
+// read, so no read waits behind a branch; those from S on are not used).
+template <int MAXS, int RA, int PITCH>
+__device__ __forceinline__ float gather(float s, const float* red, int S, int row, int col) {
+  float v[MAXS];
+#pragma unroll
+  for (int w = 0; w < MAXS; ++w) v[w] = red[(w * RA + row) * PITCH + col];
+#pragma unroll
+  for (int w = 0; w < MAXS; ++w) s = w < S ? s + v[w] : s;
   return s;
 }
 
@@ -224,29 +302,37 @@ __device__ __forceinline__ void tile_of(int id, int nrow, int ncol, int& rb, int
   }
 }
 
-// Stages per wave for F fragments of both operands.
-template <int F>
+// Stages per wave for ROWS stage rows of both operands.
+template <int ROWS>
 constexpr int stages() {
-  constexpr int lds = 160 * 1024 / (NW * F * 16 * PIECE);
-  constexpr int wait = 63 / (HALVES * F) + 1;  // (NST - 1) stages' copies within vmcnt's range
+  constexpr int lds = 160 * 1024 / (NW * ROWS * PIECE);
+  constexpr int wait = 63 / (ROWS / RPC) + 1;  // (NST - 1) stages' copies within vmcnt's range
   constexpr int fit = lds < wait ? lds : wait;
   return fit < 6 ? fit : 6;
 }
 
-// Forward step.  Grid: cdiv(B, 16 MF) * (H / 16) blocks.
-template <typename E, int MF>
-__global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, const E* __restrict__ x,
+// LDS bytes of the four rings, or of the partial sums of Q runs per wave.
+template <int RA, int RB, int NST, int PITCH, int Q>
+constexpr size_t smem_bytes() {
+  constexpr size_t ring = static_cast<size_t>(NW) * NST * (RA + RB) * PIECE;
+  constexpr size_t red = sizeof(float) * NW * Q * RA * PITCH;
+  return ring > red ? ring : red;
+}
+
+// Forward step.  Grid: cdiv(B, ROWS) * (H / 16) blocks.  S partial sums of
+// kps pieces each (bf16), or S = 0 (fp32).
+template <typename E, int ROWS>
+__global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, int S, int kps, const E* __restrict__ x,
                                                        const E* __restrict__ h_prev, const E* __restrict__ Wx,
                                                        const E* __restrict__ Wh, const float* __restrict__ bias,
                                                        const float* __restrict__ c_prev,
                                                        const uint8_t* __restrict__ reset_t, E* __restrict__ h_out,
                                                        float* __restrict__ c_out, E* __restrict__ gates_out) {
-  constexpr int ROWS = 16 * MF, PITCH = 4 * UNITS + 4;
+  constexpr int COLS = 4 * UNITS, PITCH = COLS + 4;
+  constexpr int Q = sizeof(E) == 2 ? 2 : 1;
   constexpr int EPT = ROWS * UNITS / NT;  // elements per thread
-  constexpr int NST = stages<MF + 4>();
-  constexpr size_t RED = sizeof(float) * NW * ROWS * PITCH;
-  constexpr size_t RING = ring_bytes<MF, 4, NST>();
-  __shared__ __attribute__((aligned(1024))) char smem[RED > RING ? RED : RING];
+  constexpr int NST = stages<ROWS + COLS>();
+  __shared__ __attribute__((aligned(1024))) char smem[smem_bytes<ROWS, COLS, NST, PITCH, Q>()];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int rb, cb;
@@ -254,17 +340,18 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, cons
   const int m0 = rb * ROWS, u0 = cb * UNITS;
   constexpr int EPP = PIECE / sizeof(E);
   const uint32_t ldx = D * sizeof(E), ldh = H * sizeof(E);
+  const int n = (D + H) / EPP;
 
-  Operand<MF> oa;
-  Operand<4> ob;
-  oa.init(x, h_prev, B, ldx, ldh, D / EPP, (D + H) / EPP, lane, [&](int r, bool& masked) {
+  Operand<ROWS> oa;
+  Operand<COLS> ob;
+  oa.init(x, h_prev, B, ldx, ldh, D / EPP, n, lane, [&](int r, bool& masked) {
     const int row = m0 + r;
     masked = reset_t != nullptr && row < B && reset_t[row] != 0;
     return static_cast<uint32_t>(row);
   });
-  ob.init(Wx, Wh, 4 * H, ldx, ldh, D / EPP, (D + H) / EPP, lane,
+  ob.init(Wx, Wh, 4 * H, ldx, ldh, D / EPP, n, lane,
           [&](int r, bool&) { return static_cast<uint32_t>((r >> 4) * H + u0 + (r & 15)); });
-  // what the cell needs, requested ahead of the product (reset flags as bytes)
+  // what the cell needs, requested ahead of the product
   float cp[EPT], bs[4];
   const int uc = tid & (UNITS - 1);
 #pragma unroll
@@ -275,15 +362,13 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, cons
 #pragma unroll
   for (int g = 0; g < 4; ++g) bs[g] = bias[g * H + u0 + uc];
 
-  f4_t acc[MF][4];
-#pragma unroll
-  for (int a = 0; a < MF; ++a)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) acc[a][g] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  k_loop<E, NST>(oa, ob, smem, wave, lane, acc);
+  typename Frag<E>::acc_t acc[Q][ROWS / Frag<E>::R][COLS / Frag<E>::R];
+  zero_acc(acc);
+  k_loop<E, NST>(oa, ob, runs_of(S, kps, n, wave), smem, wave, lane, acc);
   float* red = reinterpret_cast<float*>(smem);
   __syncthreads();  // every wave is done with its ring
-  park<MF, 4, PITCH>(acc, red, wave, lane);
+  const int sums = Q == 1 ? NW : S;
+  park<E, ROWS, PITCH>(acc, red, sums, wave, lane);
   __syncthreads();
 
 #pragma unroll
@@ -293,13 +378,15 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, cons
     if (row >= B) continue;
     float p[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) p[g] = gather<ROWS, PITCH>(red, r, g * UNITS + uc) + bs[g];
-    const float cpv = (reset_t != nullptr && reset_t[row] != 0) ? 0.0f : cp[i];
+    for (int g = 0; g < 4; ++g) p[g] = gather<Q * NW, ROWS, PITCH>(bs[g], red, sums, r, g * UNITS + uc);
+    const float keep = (reset_t != nullptr && reset_t[row] != 0) ? 0.0f : 1.0f;
+    const float cpv = keep * cp[i];
     const float ig = sigmoid_f(p[0]), fg = sigmoid_f(p[1]), gg = tanh_f(p[2]), og = sigmoid_f(p[3]);
     const float c = fg * cpv + ig * gg;
+    const float h = og * tanh_f(c);
     const size_t hj = static_cast<size_t>(row) * H + u0 + uc;
     c_out[hj] = c;
-    h_out[hj] = elem<E>::from_f32(og * tanh_f(c));
+    h_out[hj] = elem<E>::from_f32(h);
     if (gates_out != nullptr) {
       E* gp = gates_out + static_cast<size_t>(row) * 4 * H + u0 + uc;
       gp[0] = elem<E>::from_f32(ig);
@@ -314,65 +401,61 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, cons
 // gradient: P_t [B][ldp] against Wf [H][ldp]; K0 = 0 without) and source 1
 // (dG_{t+1} [B][4H] against W_h^T [H][4H]; absent where dG_next is null), the
 // rows under reset_next zero in source 1; then the cell as lstm_bwd_cell.
-// Grid: (time-padded rows / (16 MF)) * (H / (16 NF)) blocks; a block past B
+// Grid: (time-padded rows / T) * (H / T) blocks of T x T; a block past B
 // writes the zeros of its padding columns.  Partial column sums of dG go to
-// row rb * ROWS / 32 of db_part (one row per 32 batch rows).
-template <typename E, int MF, int NF>
+// row rb * T / 32 of db_part (one row per 32 batch rows).  S, kps as in the
+// forward step.
+template <typename E, int T>
 __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
-    int B, int Bp, int H, const E* __restrict__ P, const E* __restrict__ Wf, int K0, const E* __restrict__ dG_next,
+    int B, int Bp, int H, int S, int kps, const E* __restrict__ P, const E* __restrict__ Wf, int K0, const E* __restrict__ dG_next,
     const E* __restrict__ WhT, const uint8_t* __restrict__ reset_next, const float* __restrict__ dh_t,
     const float* __restrict__ dh_extra, const float* dc_in, float* dc_out, const E* __restrict__ gates_t,
     const float* __restrict__ c_t, const float* __restrict__ c_prev, const uint8_t* __restrict__ reset_t,
     E* __restrict__ dG_t, float* __restrict__ db_part, int db_accumulate, E* __restrict__ dGT, size_t ldt, int col0) {
-  constexpr int ROWS = 16 * MF, COLS = 16 * NF, PITCH = COLS + 4;
-  constexpr int RG = NT / COLS;         // row groups: a thread takes rows rg, rg + RG, ...
-  constexpr int EPT = ROWS / RG;        // rows per thread
-  constexpr int TP = ROWS + 8;          // row pitch of the transposed tile (bf16)
-  static_assert(EPT >= 1 && ROWS % 32 == 0 && 4 * COLS <= NT, "whole rows of db_part, a thread per column and gate");
-  constexpr int NST = stages<MF + NF>();
-  constexpr size_t RED = sizeof(float) * NW * ROWS * PITCH;
-  constexpr size_t SUMS = sizeof(float) * RG * 4 * COLS;
-  constexpr size_t TQ = sizeof(E) == 2 ? sizeof(uint16_t) * 4 * COLS * TP : 0;
-  constexpr size_t RING = ring_bytes<MF, NF, NST>();
-  constexpr size_t SMEM = RED > RING ? RED : RING;
+  constexpr int PITCH = T + 4;
+  constexpr int Q = sizeof(E) == 2 ? 2 : 1;
+  constexpr int RG = NT / T;   // row groups: a thread takes rows rg EPT .. rg EPT + EPT - 1 of one column
+  constexpr int EPT = T / RG;  // rows per thread
+  constexpr int TP = T + 8;    // row pitch of the transposed tile (bf16)
+  static_assert(T % 32 == 0 && EPT % 2 == 0 && 4 * T <= NT, "whole rows of db_part, row pairs, a thread per sum");
+  constexpr int NST = stages<2 * T>();
+  constexpr size_t SMEM = smem_bytes<T, T, NST, PITCH, Q>();
+  constexpr size_t SUMS = sizeof(float) * (T / 2) * 4 * T;  // of row pairs
+  constexpr size_t TQ = sizeof(E) == 2 ? sizeof(uint16_t) * 4 * T * TP : 0;
   static_assert(SUMS + TQ <= SMEM, "the epilogue's arrays reuse the ring");
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   float* red = reinterpret_cast<float*>(smem);
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int rb, cb;
-  tile_of(blockIdx.x, Bp / ROWS, H / COLS, rb, cb);
-  const int m0 = rb * ROWS, j0 = cb * COLS;
+  tile_of(blockIdx.x, Bp / T, H / T, rb, cb);
+  const int m0 = rb * T, j0 = cb * T;
   const int G = 4 * H;
 
-  f4_t acc[MF][NF];
-#pragma unroll
-  for (int a = 0; a < MF; ++a)
-#pragma unroll
-    for (int b = 0; b < NF; ++b) acc[a][b] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  typename Frag<E>::acc_t acc[Q][T / Frag<E>::R][T / Frag<E>::R];
+  zero_acc(acc);
   if (m0 < B) {
     constexpr int EPP = PIECE / sizeof(E);
     const uint32_t ld0 = K0 * sizeof(E), ld1 = G * sizeof(E);
     const int n = (K0 + (dG_next != nullptr ? G : 0)) / EPP;
-    Operand<MF> oa;
-    Operand<NF> ob;
+    Operand<T> oa, ob;
     oa.init(P, dG_next, B, ld0, ld1, K0 / EPP, n, lane, [&](int r, bool& masked) {
       const int row = m0 + r;
       masked = reset_next != nullptr && row < B && reset_next[row] != 0;
       return static_cast<uint32_t>(row);
     });
     ob.init(Wf, WhT, H, ld0, ld1, K0 / EPP, n, lane, [&](int r, bool&) { return static_cast<uint32_t>(j0 + r); });
-    k_loop<E, NST>(oa, ob, smem, wave, lane, acc);
+    k_loop<E, NST>(oa, ob, runs_of(S, kps, n, wave), smem, wave, lane, acc);
   }
 
   // the cell's inputs, requested before the partial sums meet
-  const int jc = tid % COLS, rg = tid / COLS;
+  const int jc = tid % T, rg = tid / T;
   const int j = j0 + jc;
   float dhv[EPT], exv[EPT], dcv[EPT], ctv[EPT], cpv[EPT], gin[EPT][4];
   bool rt[EPT];
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const int bc = min(m0 + rg + i * RG, B - 1);
+    const int bc = min(m0 + rg * EPT + i, B - 1);
     const size_t hj = static_cast<size_t>(bc) * H + j;
     const size_t gj = static_cast<size_t>(bc) * G + j;
     dhv[i] = dh_t != nullptr ? dh_t[hj] : 0.0f;
@@ -385,22 +468,25 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
     rt[i] = reset_t != nullptr && reset_t[bc] != 0;
   }
   __syncthreads();  // every wave is done with its ring
-  park<MF, NF, PITCH>(acc, red, wave, lane);
+  const int sums_n = Q == 1 ? NW : S;
+  park<E, T, PITCH>(acc, red, sums_n, wave, lane);
   __syncthreads();
   float rec[EPT];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) rec[i] = gather<ROWS, PITCH>(red, rg + i * RG, jc);
+  for (int i = 0; i < EPT; ++i) rec[i] = gather<Q * NW, T, PITCH>(0.0f, red, sums_n, rg * EPT + i, jc);
   __syncthreads();  // the partial sums' memory is free
 
-  float* sums = reinterpret_cast<float*>(smem);              // [RG][4][COLS]
-  uint16_t* tq = reinterpret_cast<uint16_t*>(smem + SUMS);   // [4 COLS][TP]
+  float* sums = reinterpret_cast<float*>(smem);             // [T / 2][4][T]
+  uint16_t* tq = reinterpret_cast<uint16_t*>(smem + SUMS);  // [4 T][TP]
   float sd[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const int r = rg + i * RG, b = m0 + r;
+    const int r = rg * EPT + i, b = m0 + r;
     float d[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (b < B) {
-      const float dh = dhv[i] + exv[i] + rec[i];
+      float dh = dhv[i];
+      if (dh_extra != nullptr) dh = dh + exv[i];
+      dh = dh + rec[i];
       const float ig = gin[i][0], fg = gin[i][1], gg = gin[i][2], og = gin[i][3];
       const float tc = tanh_f(ctv[i]);
       const float keep = rt[i] ? 0.0f : 1.0f;
@@ -418,30 +504,34 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
     }
     if constexpr (sizeof(E) == 2) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) tq[(g * COLS + jc) * TP + r] = f32_to_bf16_bits(d[g]);
+      for (int g = 0; g < 4; ++g) tq[(g * T + jc) * TP + r] = f32_to_bf16_bits(d[g]);
+    }
+    if (i & 1) {  // a row pair is done
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        sums[((r >> 1) * 4 + g) * T + jc] = sd[g];
+        sd[g] = 0.0f;
+      }
     }
   }
-#pragma unroll
-  for (int g = 0; g < 4; ++g) sums[(rg * 4 + g) * COLS + jc] = sd[g];
   __syncthreads();
-  if (tid < 4 * COLS) {
-    const int g = tid / COLS, jl = tid % COLS;
-    float s = 0.0f;
+  if (tid < 4 * T) {
+    const int g = tid / T, jl = tid % T;
 #pragma unroll
-    for (int q = 0; q < RG; ++q) s += sums[(q * 4 + g) * COLS + jl];
-    float* p = db_part + static_cast<size_t>(m0 / 32) * G + g * static_cast<size_t>(H) + j0 + jl;
-    *p = db_accumulate ? *p + s : s;  // the same block owns this entry at every step
-    if (!db_accumulate) {
+    for (int k = 0; k < T / 32; ++k) {
+      float s = 0.0f;
 #pragma unroll
-      for (int q = 1; q < ROWS / 32; ++q) p[static_cast<size_t>(q) * G] = 0.0f;
+      for (int q = 0; q < 16; ++q) s += sums[((k * 16 + q) * 4 + g) * T + jl];
+      float* p = db_part + static_cast<size_t>(m0 / 32 + k) * G + g * static_cast<size_t>(H) + j0 + jl;
+      *p = db_accumulate ? *p + s : s;  // the same block owns this entry at every step
     }
   }
   if constexpr (sizeof(E) == 2) {
-    constexpr int CPR = ROWS / 8;  // 16-byte pieces per transposed row
-    for (int e = tid; e < 4 * COLS * CPR; e += NT) {
-      const int u = e / CPR, c = e % CPR;
+    constexpr int CPT = T / 8;  // 16-byte pieces per transposed row
+    for (int e = tid; e < 4 * T * CPT; e += NT) {
+      const int u = e / CPT, c = e % CPT;
       const uint4 v = *reinterpret_cast<const uint4*>(tq + u * TP + 8 * c);
-      *reinterpret_cast<uint4*>(dGT + (static_cast<size_t>(u / COLS) * H + j0 + u % COLS) * ldt + col0 + m0 + 8 * c) = v;
+      *reinterpret_cast<uint4*>(dGT + (static_cast<size_t>(u / T) * H + j0 + u % T) * ldt + col0 + m0 + 8 * c) = v;
     }
   }
 }
@@ -455,23 +545,27 @@ inline bool offsets_fit(size_t esize, int B, int D, int H) {
 
 }  // namespace step
 
-// Row fragments per block of the forward step: the tallest tile that still
-// gives every CU a block (a taller tile reads the weights fewer times).
-inline int step_fwd_mf(int B, int H) {
-  for (int mf = 4; mf > 1; mf /= 2)
-    if (static_cast<long long>((B + 16 * mf - 1) / (16 * mf)) * (H / step::UNITS) >= 256) return mf;
-  return 1;
+// Rows per block of the forward step: the tallest tile that still gives every
+// CU a block (a taller tile reads the weights fewer times).
+template <typename E>
+inline int step_fwd_rows(int B, int H) {
+  for (int rows = 64; rows > step::Frag<E>::R; rows /= 2)
+    if (static_cast<long long>((B + rows - 1) / rows) * (H / step::UNITS) >= 256) return rows;
+  return step::Frag<E>::R;
 }
 
+// S, kps: the K split of the separate product (bf16), 0 in fp32.
 template <typename E>
-inline void launch_step_fwd(int B, int D, int H, const E* x, const E* h_prev, const E* Wx, const E* Wh,
+inline void launch_step_fwd(int B, int D, int H, int S, int kps, const E* x, const E* h_prev, const E* Wx, const E* Wh,
                             const float* bias, const float* c_prev, const uint8_t* reset_t, E* h, float* c, E* gates,
                             hipStream_t s) {
-  const int mf = step_fwd_mf(B, H);
-  auto kernel = mf == 4 ? step::lstm_step_fwd<E, 4> : mf == 2 ? step::lstm_step_fwd<E, 2> : step::lstm_step_fwd<E, 1>;
-  const unsigned blocks = static_cast<unsigned>((B + 16 * mf - 1) / (16 * mf)) * (H / step::UNITS);
-  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(step::NT), 0, s, B, D, H, x, h_prev, Wx, Wh, bias, c_prev, reset_t, h,
-                     c, gates);
+  const int rows = step_fwd_rows<E>(B, H);
+  auto kernel = rows == 64 ? step::lstm_step_fwd<E, 64> : step::lstm_step_fwd<E, 32>;
+  if constexpr (sizeof(E) == 4)
+    if (rows == 16) kernel = step::lstm_step_fwd<E, 16>;
+  const unsigned blocks = static_cast<unsigned>((B + rows - 1) / rows) * (H / step::UNITS);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(step::NT), 0, s, B, D, H, S, kps, x, h_prev, Wx, Wh, bias, c_prev,
+                     reset_t, h, c, gates);
 }
 
 }  // namespace o5

@@ -746,10 +746,9 @@ static PpoWs ppo_ws(o5_dtype dt, int N, int H, int A1, int unit_nk = 0, int unit
   // (1.61 against 1.50 ms for the call with 189 units)
   w.rows_t = w.ldh <= 256;
   w.nblk_t = cdiv(N, kRtRows);
-  w.plan_z = plan_gemm(bf, N, A1, H);
-  w.plan_w = plan_gemm(false, A1, H, N);  // fp32 dWp (bf16: the pair product below)
-  w.plan_h = plan_gemm(bf, N, H, 2 * w.ldh);
-  w.plan_h.splits = 1;
+  w.plan_z = plan_gemm(bf, N, A1, H, Split::kStep);
+  w.plan_w = plan_gemm_f32(A1, H, N);  // fp32 dWp (bf16: the pair product below)
+  w.plan_h = plan_gemm(bf, N, H, 2 * w.ldh, Split::kOne);
   w.wsplits = 1;
   if (bf) {
     // dWp: M = 2 A1p, N = H, K = N: split K so the grid has about 256

@@ -230,8 +230,7 @@ static PreBwdWs prelstm_bwd_ws(o5_dtype dt, int N, int D) {
 template <typename E>
 static void prelstm_fwd_impl(int N, int Do, int D, const E* o, const E* W, const float* b, float* y, E* x,
                              hipStream_t s) {
-  GemmPlan plan = plan_gemm(sizeof(E) == 2, N, D, Do);
-  plan.splits = 1;  // the epilogue needs whole sums
+  const GemmPlan plan = plan_gemm(sizeof(E) == 2, N, D, Do, Split::kOne);  // the epilogue needs whole sums
   KRows2<E> al{o, nullptr, nullptr, Do, 0, Do, Do, N};
   KRows2<E> bl{W, nullptr, nullptr, Do, 0, Do, Do, D};
   run_gemm(plan, al, bl, EpiBiasRelu{y, b, D}, N, D, Do, s);
@@ -249,8 +248,7 @@ static void prelstm_bwd_impl(int N, int Do, int D, const E* o, const float* y, c
                      dx, dpre, dbpart);
   hipLaunchKernelGGL(colsum_rows4, dim3(cdiv(D, 64)), dim3(256), 0, s, w.nby, D, dbpart, db);
   // dW[d, k] = sum_n dpre[n, d] o[n, k]: both operands I-contiguous
-  GemmPlan plan = plan_gemm(sizeof(E) == 2, D, Do, N);
-  plan.splits = 1;
+  const GemmPlan plan = plan_gemm_icols(sizeof(E) == 2, D, Do);
   ICols2<E> al{dpre, nullptr, nullptr, nullptr, D, 0, D, D, N, 0};
   ICols2<E> bl{o, nullptr, nullptr, nullptr, Do, 0, Do, Do, N, 0};
   run_gemm(plan, al, bl, EpiStoreF32{dW, Do, 0}, D, Do, N, s);

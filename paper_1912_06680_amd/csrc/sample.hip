@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(kSampleWaves * 64) gumbel_sample_rows(
 // zpart, then the unit-selection head's scratch (if any) at *unit_off.
 static size_t sample_ws_bytes(o5_dtype dt, int B, int H, int A1, GemmPlan* plan, int unit_nk, int unit_d,
                               UnitWs* uw, size_t* unit_off) {
-  *plan = plan_gemm(dt == O5_BF16, B, A1, H);
+  *plan = plan_gemm(dt == O5_BF16, B, A1, H, Split::kFree);
   size_t o = align_up(static_cast<size_t>(plan->splits) * B * A1 * 4);
   *unit_off = o;
   if (unit_d > 0) {

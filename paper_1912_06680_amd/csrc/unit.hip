@@ -195,8 +195,7 @@ void unit_forward(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, cons
   float* q = reinterpret_cast<float*>(ws + w.q);
   float* zext = reinterpret_cast<float*>(ws + w.zext);
   const int d = w.d;
-  GemmPlan plan = plan_gemm(dt == O5_BF16, N, d, H);
-  plan.splits = 1;
+  const GemmPlan plan = plan_gemm(dt == O5_BF16, N, d, H, Split::kOne);
   const dim3 grid(N);
   if (dt == O5_BF16) {
     KRows2<uint16_t> al{static_cast<const uint16_t*>(h), nullptr, nullptr, H, 0, H, H, N};

@@ -1,7 +1,7 @@
-"""GPU: the fp32 matrix-unit engine at the edges of its tiles, through the
-pre-LSTM layer (forward: two K-contiguous operands; weight gradient: two
-I-contiguous operands with a reduction length that is no multiple of the K
-tile), on 64 x 64 and 128 x 128 tiles.
+"""GPU: the matrix engines at the edges of their tiles, through the pre-LSTM
+layer (fp32 forward: two K-contiguous operands; fp32 weight gradient: two
+I-contiguous ones with a reduction length that is no multiple of the K tile;
+bf16 forward: the tall tiles).
 
 Bound: a sum of K fp32 products in any order is within (K + 2) 2^-24
 sum_k |a_k b_k| of the exact one (each product and each add rounds once)."""
@@ -58,3 +58,24 @@ def test_layer_products_within_the_rounding_bound(T, B, Do, D):
     dpre[:, 0, :P] = tot
     dpre = dpre.reshape(N, D).double()
     _within("dW", dW, dpre.t() @ o.double(), dpre.abs().t() @ o.double().abs(), N)
+
+
+@pytest.mark.parametrize("B,Do,D", [
+    (4805, 64, 4096),   # 16 x 16 tiles of 320 x 256, the last row tile with 5 rows; one K tile
+    (5000, 192, 4096),  # the last row tile with 200 rows; three K tiles
+    (5120, 320, 4032),  # whole row tiles, the last column tile with 192 columns
+])
+def test_tall_bf16_tiles_within_the_rounding_bound(B, Do, D):
+    """320 x 256 tiles of the bf16 engine: products of bf16 values are exact
+    in fp32, so the same bound holds for the sum (and y is stored in fp32)."""
+    need_gpu()
+    banner(f"bf16 tall tiles B={B} Do={Do} D={D}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B)
+    o = torch.randn((B, Do), generator=g, device="cuda").bfloat16()
+    W = torch.randn((D, Do), generator=g, device="cuda").bfloat16()
+    b = torch.randn(D, generator=g, device="cuda")
+    y, x = torch.full((B, D), -7.0, device="cuda"), torch.empty((B, D), dtype=torch.bfloat16, device="cuda")
+    o5.o5_prelstm_fwd(o5.O5_BF16, 1, B, Do, D, o, W, b, y, x)
+    pre = o.double() @ W.double().t() + b.double()
+    _within("y", y, torch.relu(pre), o.double().abs() @ W.double().abs().t() + b.double().abs(), Do + 1)
