@@ -34,6 +34,27 @@ static __global__ void __launch_bounds__(256) sum_hilo_splits(int S, int A1, int
   out[i] = v;
 }
 
+// The same where the pair also carries a unit head's dq: rows a < A1 go to
+// dWp, rows A1p .. A1p + d - 1 to dWq; ldh rows per half.
+static __global__ void __launch_bounds__(256) sum_hilo_heads(int S, int A1, int A1p, int d, int ldh, int H,
+                                                            const float* __restrict__ part, float* __restrict__ dWp,
+                                                            float* __restrict__ dWq) {
+  const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const size_t np = static_cast<size_t>(A1) * H, nq = static_cast<size_t>(d) * H;
+  if (i >= np + nq) return;
+  const size_t hs = static_cast<size_t>(ldh) * H;  // offset of the lo half
+  const size_t e = i < np ? i : static_cast<size_t>(A1p) * H + (i - np);
+  float v = 0.0f;
+  for (int s2 = 0; s2 < S; ++s2) {
+    const float* p = part + static_cast<size_t>(s2) * 2 * hs;
+    v += p[e] + p[hs + e];
+  }
+  if (i < np)
+    dWp[i] = v;
+  else
+    dWq[i - np] = v;
+}
+
 // ------------------------------------------------- unit-selection head
 // Head `unit->head` scored against per-row unit embeddings (o5_unit_head):
 // q = h Wq^T + bq, logits <q[n], E[n, u]>.  Scratch of the loss and the
@@ -46,6 +67,7 @@ static __global__ void __launch_bounds__(256) sum_hilo_splits(int S, int A1, int
 struct UnitWs {
   size_t q, zext, dzext, dq, dqT, wpart, dbpart, total;
   int d, dp, nk, ldT, wsplits, nchunks;
+  int qsplits;  // partial sums of the query that the loss's one-pass kernel adds
 };
 
 // Validates the head description (loss: with the gradient outputs).
@@ -53,6 +75,11 @@ int check_unit(const char* fn, const HeadsMeta& hm, const o5_unit_head* u, bool 
 UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss);
 void unit_forward(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
                   hipStream_t s);
+// The query's partial sums only (for the one-pass kernel), at q [qsplits][N][d].
+void unit_query(o5_dtype dt, int N, int H, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
+                hipStream_t s);
+// dWq = dq^T h from the fp32 dq at w.dq.
+void unit_weight_grad_f32(int N, int H, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w, hipStream_t s);
 void unit_grad(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
                uint16_t* dzhi, uint16_t* dzlo, int col0, int ld, hipStream_t s);
 

@@ -24,6 +24,7 @@
 #include "gemm_plan.h"
 #include "heads.h"
 #include "reduce.h"
+#include "unit_rows.h"
 
 namespace o5 {
 
@@ -707,10 +708,12 @@ __global__ void __launch_bounds__(256) pair_weights_t(int A1, int A1p, int ldh, 
 }
 
 // stats from the summed block partials (sums = [dz column sums (A1) | row
-// stat sums (kStatCols)]); also copies the bias gradient out.
+// stat sums (kStatCols) | dq column sums (d, one-pass unit heads)]); also
+// copies the bias gradients out.
 __global__ void ppo_finalize(int A1, const float* __restrict__ sums, float invN, float vf_coef, float ent_coef,
-                             float* __restrict__ stats, float* __restrict__ dbp) {
+                             float* __restrict__ stats, float* __restrict__ dbp, int d, float* __restrict__ dbq) {
   for (int a = threadIdx.x; a < A1; a += blockDim.x) dbp[a] = sums[a];
+  for (int j = threadIdx.x; j < d; j += blockDim.x) dbq[j] = sums[A1 + kStatCols + j];
   if (threadIdx.x != 0) return;
   const float* ss = sums + A1;
   const float pg = -ss[0] * invN, vf = ss[1] * invN, ent = ss[2] * invN;
@@ -724,12 +727,15 @@ __global__ void ppo_finalize(int A1, const float* __restrict__ sums, float invN,
   stats[7] = ss[6];
 }
 
+static_assert(kUrStat == kStatCols, "one layout of the partial sums");
+
 struct PpoWs {
   size_t zpart, dz, part, sums, wpart, dzp, wT, unit, total;
   UnitWs uw;  // the unit-selection head's scratch, at offset unit (if any)
   GemmPlan plan_z, plan_w, plan_h;
   int nblk, A1, A1p, ldh, wsplits;  // ldh: row length of the (hi, lo) pair, A1p + the unit head's dp
   bool rows_t;  // the row kernel with one thread per row (ppo_rows_t)
+  bool one_pass;  // a unit head whose rows unit_rows takes
   int nblk_t;   // its blocks (= partial rows)
 };
 
@@ -740,6 +746,7 @@ static PpoWs ppo_ws(o5_dtype dt, int N, int H, int A1, int unit_nk = 0, int unit
   w.A1p = cdiv(A1, 64) * 64;  // padded logit count: a multiple of the K tile
   w.ldh = w.A1p + (unit_d > 0 ? cdiv(unit_d, 64) * 64 : 0);
   w.nblk = cdiv(N, kRowsPerBlock);
+  w.one_pass = unit_d > 0 && unit_rows_fits(unit_nk, unit_d);
   // the thread-per-row kernel takes up to 256 logit columns; where a unit
   // head widens the pair past 256 columns its long head (one lane runs a
   // head's columns serially) made it slower than the wave-per-row kernel
@@ -755,6 +762,13 @@ static PpoWs ppo_ws(o5_dtype dt, int N, int H, int A1, int unit_nk = 0, int unit
     // blocks, each with at least 8 K tiles of 32
     const int tiles = cdiv(2 * w.A1p, 256) * cdiv(H, 256);
     w.wsplits = std::max(1, std::min(cdiv(256, tiles), cdiv(N, 32) / 8));
+    if (w.one_pass) {
+      // a unit head's product covers its dq columns too: at most 256 blocks,
+      // a single round of them (N = 9600, H = 4096, 768 columns: 6 splits
+      // 114 us in two rounds, 5 splits 75)
+      const int t1 = cdiv(2 * w.ldh, 256) * cdiv(H, 256);
+      w.wsplits = std::max(1, std::min(256 / t1, cdiv(N, 32) / 8));
+    }
   }
   size_t o = 0;
   w.zpart = o;
@@ -762,11 +776,13 @@ static PpoWs ppo_ws(o5_dtype dt, int N, int H, int A1, int unit_nk = 0, int unit
   w.dz = o;
   o += align_up(static_cast<size_t>(N) * A1 * 4);
   w.part = o;
-  o += align_up(static_cast<size_t>(w.nblk) * (A1 + kStatCols) * 4);
+  // (the one-pass kernel's rows also hold the d column sums of dq)
+  const int pcols = A1 + kStatCols + (w.one_pass ? unit_d : 0);
+  o += align_up(static_cast<size_t>(w.one_pass ? unit_rows_grid(N) : w.nblk) * pcols * 4);
   w.sums = o;
-  o += align_up(static_cast<size_t>(A1 + kStatCols) * 4);
+  o += align_up(static_cast<size_t>(pcols) * 4);
   w.wpart = o;
-  o += align_up(bf ? static_cast<size_t>(w.wsplits) * 2 * w.A1p * H * 4
+  o += align_up(bf ? static_cast<size_t>(w.wsplits) * 2 * (w.one_pass ? w.ldh : w.A1p) * H * 4
                         : static_cast<size_t>(w.plan_w.splits) * A1 * H * 4);
   w.dzp = w.wT = 0;
   if (bf) {
@@ -861,7 +877,10 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
   constexpr o5_dtype dt = sizeof(E) == 2 ? O5_BF16 : O5_F32;
   if (unit != nullptr) {  // the unit-selection head's logits
     kext = unit->head;
-    unit_forward(dt, N, H, w.uw.nk, *unit, h, uws, w.uw, s);
+    if (w.one_pass)
+      unit_query(dt, N, H, *unit, h, uws, w.uw, s);
+    else
+      unit_forward(dt, N, H, w.uw.nk, *unit, h, uws, w.uw, s);
     zext = reinterpret_cast<const float*>(uws + w.uw.zext);
     dzext = reinterpret_cast<float*>(uws + w.uw.dzext);
   }
@@ -873,7 +892,38 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
   }
   const int S = w.plan_z.splits;
   const int cpl = cdiv(A1, 64);
-  if (w.rows_t && w.A1p <= 128)
+  if (w.one_pass) {
+    UnitRowsArgs g{};
+    g.N = N;
+    g.A1 = A1;
+    g.S = S;
+    g.Sq = w.uw.qsplits;
+    g.d = unit->d;
+    g.dp = w.ldh - w.A1p;
+    g.kext = kext;
+    g.zpart = zpart;
+    g.bp = bp;
+    g.qpart = reinterpret_cast<const float*>(uws + w.uw.q);
+    g.bq = unit->bq;
+    g.act = act;
+    g.logp_old = logp_old;
+    g.adv = adv;
+    g.ret = ret;
+    g.mask = mask;
+    g.avail = avail;
+    g.hm = hm;
+    g.clip_eps = hp.clip_eps;
+    g.vf_coef = hp.vf_coef;
+    g.ent_coef = hp.ent_coef;
+    g.invN = invN;
+    g.dz = dz;
+    g.dq = sizeof(E) == 2 ? nullptr : reinterpret_cast<float*>(uws + w.uw.dq);
+    g.pair = dzhi;
+    g.A1p = w.A1p;
+    g.ldh = w.ldh;
+    g.part = part;
+    launch_unit_rows(g, static_cast<const E*>(unit->E), w.uw.nk, s);
+  } else if (w.rows_t && w.A1p <= 128)
     hipLaunchKernelGGL(ppo_rows_t<128>, dim3(w.nblk_t), dim3(kRtThreads), 0, s, N, A1, S, zpart, bp, act, logp_old,
                        adv, ret, mask, avail, hm, zext, dzext, kext, hp.clip_eps, hp.vf_coef, hp.ent_coef, invN, dz,
                        part, dzhi, dzlo, w.A1p, 2 * w.ldh);
@@ -903,7 +953,7 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
     int d = 0;
     if (unit != nullptr) {
       // dq (hi, lo) into columns A1p .. ldh - 1 of the pair, Wq into the same columns of wT
-      unit_grad(dt, N, H, w.uw.nk, *unit, h, uws, w.uw, dzhi, dzlo, A1p, 2 * ldh, s);
+      if (!w.one_pass) unit_grad(dt, N, H, w.uw.nk, *unit, h, uws, w.uw, dzhi, dzlo, A1p, 2 * ldh, s);
       Wq = static_cast<const uint16_t*>(unit->Wq);
       d = unit->d;
     }
@@ -914,7 +964,15 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
       EpiStoreF32 epi{dh, H, 0};
       run_gemm(w.plan_h, al, bl, epi, N, H, 2 * ldh, s);
     }
-    {
+    if (w.one_pass) {
+      // the whole pair at once: [dWp_hi ; dWq_hi ; dWp_lo ; dWq_lo], h read once
+      ICols2<uint16_t> al{dzhi, nullptr, nullptr, nullptr, 2 * ldh, 0, 2 * ldh, 2 * ldh, N, 0};
+      ICols2<uint16_t> bl{h, nullptr, nullptr, nullptr, H, 0, H, H, N, 0};
+      EpiStoreF32 epi{wpart, H, static_cast<size_t>(2) * ldh * H};
+      launch_gemm_bf16_dma(al, bl, epi, 2 * ldh, H, N, w.wsplits, s);
+      hipLaunchKernelGGL(sum_hilo_heads, dim3(cdiv(static_cast<long long>(A1 + d) * H, 256)), dim3(256), 0, s,
+                         w.wsplits, A1, A1p, d, ldh, H, wpart, dWp, unit->dWq);
+    } else {
       // [dWp_hi ; dWp_lo] = [dz_hi | dz_lo]^T . h  (M = 2 A1p rows: the hi
       // logit columns of the pair, then its lo logit columns (a unit head's
       // dq columns in between are skipped); N = H, K = N), both operands read
@@ -934,7 +992,10 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
       EpiStoreF32 epi{dh, H, 0};
       launch_gemm_f32(al, bl, epi, N, H, A1, 1, s);
     } else {  // dh = [dz | dq] . [Wp ; Wq]
-      unit_grad(dt, N, H, w.uw.nk, *unit, h, uws, w.uw, nullptr, nullptr, 0, 0, s);
+      if (w.one_pass)
+        unit_weight_grad_f32(N, H, *unit, h, uws, w.uw, s);
+      else
+        unit_grad(dt, N, H, w.uw.nk, *unit, h, uws, w.uw, nullptr, nullptr, 0, 0, s);
       const int d = unit->d;
       const float* dq = reinterpret_cast<const float*>(uws + w.uw.dq);
       KRows2<float> al{dz, dq, nullptr, A1, d, A1, A1 + d, N};
@@ -951,9 +1012,11 @@ static int ppo_impl(int N, int H, const HeadsMeta& hm, const E* h, const E* Wp, 
     hipLaunchKernelGGL(colsum_rows, dim3(cdiv(static_cast<long long>(A1) * H, 256)), dim3(256), 0, s, w.plan_w.splits,
                        A1 * H, wpart, dWp);
   }
-  hipLaunchKernelGGL(colsum_tree, dim3(A1 + kStatCols), dim3(256), 0, s, w.rows_t ? w.nblk_t : w.nblk,
-                     A1 + kStatCols, part, sums);
-  hipLaunchKernelGGL(ppo_finalize, dim3(1), dim3(256), 0, s, A1, sums, invN, hp.vf_coef, hp.ent_coef, stats, dbp);
+  const int pcols = A1 + kStatCols + (w.one_pass ? unit->d : 0);
+  const int prows = w.one_pass ? unit_rows_grid(N) : w.rows_t ? w.nblk_t : w.nblk;
+  hipLaunchKernelGGL(colsum_tree, dim3(pcols), dim3(256), 0, s, prows, pcols, part, sums);
+  hipLaunchKernelGGL(ppo_finalize, dim3(1), dim3(256), 0, s, A1, sums, invN, hp.vf_coef, hp.ent_coef, stats, dbp,
+                     w.one_pass ? unit->d : 0, w.one_pass ? unit->dbq : nullptr);
   return check_launch("o5_ppo_loss_grad");
 }
 

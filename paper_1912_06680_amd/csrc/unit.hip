@@ -13,8 +13,11 @@
 // On the bf16 path the two products that read dq take it as a (hi, lo) pair
 // of bf16 terms (relative error ~2^-16), in row layout (written into the
 // caller's dz pair, beside dz) and transposed (K-contiguous over n) for dWq,
-// as the loss does for dz.  E is read twice, once per direction: N nk d
-// elements each way.
+// as the loss does for dz.
+//
+// The loss takes these kernels only for rows too long for unit_rows (more than
+// 4096 chunks of 8 values), which reads E once and writes dq into the pair
+// itself; here E is read twice.  The sampler needs the logits alone.
 #include "gemm_plan.h"
 #include "heads.h"
 #include "reduce.h"
@@ -161,9 +164,10 @@ UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss) {
   w.ldT = cdiv(N, kUnitT) * kUnitT;
   w.nchunks = cdiv(N, 64);
   w.wsplits = 1;
+  w.qsplits = loss ? plan_gemm(bf, N, d, H, Split::kFree).splits : 1;
   size_t o = 0;
   w.q = o;
-  o += align_up(static_cast<size_t>(N) * d * 4);
+  o += align_up(static_cast<size_t>(w.qsplits) * N * d * 4);
   w.zext = o;
   o += align_up(static_cast<size_t>(N) * nk * 4);
   if (loss) {
@@ -212,6 +216,36 @@ void unit_forward(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, cons
   }
 }
 
+void unit_weight_grad_f32(int N, int H, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
+                          hipStream_t s) {
+  // split over rows, fixed-order sum
+  const float* dq = reinterpret_cast<const float*>(ws + w.dq);
+  float* wpart = reinterpret_cast<float*>(ws + w.wpart);
+  const int d = w.d;
+  ICols2<float> al{dq, nullptr, nullptr, nullptr, d, 0, d, d, N, 0};
+  ICols2<float> bl{static_cast<const float*>(h), nullptr, nullptr, nullptr, H, 0, H, H, N, 0};
+  launch_gemm_f32(al, bl, EpiStoreF32{wpart, H, static_cast<size_t>(d) * H}, d, H, N, w.wsplits, s);
+  hipLaunchKernelGGL(colsum_rows, dim3(cdiv(static_cast<long long>(d) * H, 256)), dim3(256), 0, s, w.wsplits, d * H,
+                     wpart, u.dWq);
+}
+
+void unit_query(o5_dtype dt, int N, int H, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
+                hipStream_t s) {
+  float* q = reinterpret_cast<float*>(ws + w.q);
+  const int d = w.d;
+  const GemmPlan plan = plan_gemm(dt == O5_BF16, N, d, H, Split::kFree);
+  const EpiStoreF32 epi{q, d, static_cast<size_t>(N) * d};
+  if (dt == O5_BF16) {
+    KRows2<uint16_t> al{static_cast<const uint16_t*>(h), nullptr, nullptr, H, 0, H, H, N};
+    KRows2<uint16_t> bl{static_cast<const uint16_t*>(u.Wq), nullptr, nullptr, H, 0, H, H, d};
+    run_gemm(plan, al, bl, epi, N, d, H, s);
+  } else {
+    KRows2<float> al{static_cast<const float*>(h), nullptr, nullptr, H, 0, H, H, N};
+    KRows2<float> bl{static_cast<const float*>(u.Wq), nullptr, nullptr, H, 0, H, H, d};
+    run_gemm(plan, al, bl, epi, N, d, H, s);
+  }
+}
+
 void unit_grad(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
                uint16_t* dzhi, uint16_t* dzlo, int col0, int ld, hipStream_t s) {
   const float* dzext = reinterpret_cast<const float*>(ws + w.dzext);
@@ -240,12 +274,7 @@ void unit_grad(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, const v
     hipLaunchKernelGGL(sum_hilo_splits, dim3(cdiv(static_cast<long long>(d) * H, 256)), dim3(256), 0, s, w.wsplits, d,
                        dp, H, wpart, u.dWq);
   } else {
-    // dWq = dq^T h, split over rows, fixed-order sum
-    ICols2<float> al{dq, nullptr, nullptr, nullptr, d, 0, d, d, N, 0};
-    ICols2<float> bl{static_cast<const float*>(h), nullptr, nullptr, nullptr, H, 0, H, H, N, 0};
-    launch_gemm_f32(al, bl, EpiStoreF32{wpart, H, static_cast<size_t>(d) * H}, d, H, N, w.wsplits, s);
-    hipLaunchKernelGGL(colsum_rows, dim3(cdiv(static_cast<long long>(d) * H, 256)), dim3(256), 0, s, w.wsplits, d * H,
-                       wpart, u.dWq);
+    unit_weight_grad_f32(N, H, u, h, ws, w, s);
   }
 }
 
