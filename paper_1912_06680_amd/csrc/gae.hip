@@ -220,7 +220,11 @@ __global__ void __launch_bounds__(64) gae_laneV(int L, int S, const float* __res
   }
 }
 
-// One wave (64 lanes) per segment; blockDim = 256 holds 4 segments.
+// One wave (64 lanes) per segment; blockDim = 256 holds 4 segments.  Latency
+// bound: a chunk of up to Q steps is loaded at once and kept in registers for
+// both passes (L = 256, S = 130: 6.0 us against 8.8 with two loops of loads);
+// Q = 0 (longer segments) loops over memory.  The arithmetic is the same.
+template <int Q>
 __global__ void __launch_bounds__(256) gae_wave_per_segment(int L, int S, const float* __restrict__ r,
                                                             const float* __restrict__ v,
                                                             const uint8_t* __restrict__ done, float gamma,
@@ -233,16 +237,36 @@ __global__ void __launch_bounds__(256) gae_wave_per_segment(int L, int S, const 
   const int q = (L + 63) / 64;             // steps per lane
   const int t0 = lane * q;                 // this lane's chunk [t0, t1)
   const int t1 = min(t0 + q, L);
+  float rq[Q + 1], vq[Q + 1], vn[Q + 1];
+  uint8_t dq[Q + 1];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {  // steps past the chunk read its segment's first step and are not used
+    const int t = t1 - 1 - i;
+    const size_t idx = static_cast<size_t>(t >= t0 ? t : 0) * S_ + s;
+    rq[i] = r[idx];
+    vq[i] = v[idx];
+    vn[i] = v[idx + S_];
+    dq[i] = done[idx];
+  }
 
   // 1) reduce the chunk to A(t0) = alpha + beta * A(t1), with A(t1) unknown
   float alpha = 0.0f, beta = 1.0f;
-  for (int t = t1 - 1; t >= t0; --t) {
-    const size_t idx = static_cast<size_t>(t) * S_ + s;
-    const float nd = done[idx] ? 0.0f : 1.0f;
-    const float delta = r[idx] + gamma * nd * v[idx + S_] - v[idx];
+  auto map = [&](float ri, float vi, float vni, uint8_t di) {
+    const float nd = di ? 0.0f : 1.0f;
+    const float delta = ri + gamma * nd * vni - vi;
     const float c = gl * nd;
     alpha = delta + c * alpha;
     beta = c * beta;
+  };
+  if constexpr (Q > 0) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      if (t1 - 1 - i >= t0) map(rq[i], vq[i], vn[i], dq[i]);
+  } else {
+    for (int t = t1 - 1; t >= t0; --t) {
+      const size_t idx = static_cast<size_t>(t) * S_ + s;
+      map(r[idx], v[idx], v[idx + S_], done[idx]);
+    }
   }
   // 2) suffix scan of the maps: lane j ends with F_j = f_j o f_{j+1} o ... o f_63
   for (int d = 1; d < 64; d <<= 1) {
@@ -257,40 +281,84 @@ __global__ void __launch_bounds__(256) gae_wave_per_segment(int L, int S, const 
   float carry = __shfl_down(alpha, 1, 64);
   if (lane == 63) carry = 0.0f;
   // 3) replay the chunk from its carry-in
-  for (int t = t1 - 1; t >= t0; --t) {
+  auto replay = [&](int t, float ri, float vt, float vni, uint8_t di) {
     const size_t idx = static_cast<size_t>(t) * S_ + s;
-    const float vt = v[idx];
-    const float nd = done[idx] ? 0.0f : 1.0f;
-    const float delta = r[idx] + gamma * nd * v[idx + S_] - vt;
+    const float nd = di ? 0.0f : 1.0f;
+    const float delta = ri + gamma * nd * vni - vt;
     carry = delta + gl * nd * carry;
     adv[idx] = carry;
     ret[idx] = carry + vt;
+  };
+  if constexpr (Q > 0) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      if (t1 - 1 - i >= t0) replay(t1 - 1 - i, rq[i], vq[i], vn[i], dq[i]);
+  } else {
+    for (int t = t1 - 1; t >= t0; --t) {
+      const size_t idx = static_cast<size_t>(t) * S_ + s;
+      replay(t, r[idx], v[idx], v[idx + S_], done[idx]);
+    }
   }
 }
 
-// One thread per (t, b) of the sample layout, grid-stride; every index is
-// 64-bit, so T * B = L * S may exceed 2^31.
-__global__ void __launch_bounds__(256) segments_to_samples_kernel(int L, int S, int T,
+// The cut of [L, S] segments into samples [T, S J], J = L / T, is a transpose
+// of J x S for each t: a block moves tiles of JB samples by SB segments through
+// LDS, reading along the segments and writing along the samples (whole runs of
+// J where J <= 32), both coalesced.  Bound by memory: 53 MB at L = 256, S =
+// 11520, T = 16 in 11.2 us (4.7 TB/s); a thread per output element, reading with
+// a stride of T S elements, took 20.4.  Offsets are 64-bit, so T * B = L * S
+// may exceed 2^31.
+template <int KE>  // elements per thread and tile
+__global__ void __launch_bounds__(256) segments_to_samples_kernel(int L, int S, int T, int JB, int sb,
                                                                   const float* __restrict__ adv,
                                                                   const float* __restrict__ ret,
                                                                   const uint8_t* __restrict__ done,
                                                                   float* __restrict__ adv_s,
                                                                   float* __restrict__ ret_s,
                                                                   uint8_t* __restrict__ reset) {
-  const size_t J = static_cast<size_t>(L / T);
-  const size_t S_ = static_cast<size_t>(S);
-  const size_t B = S_ * J;
-  const size_t total = static_cast<size_t>(T) * B;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const size_t t = i / B;
-    const size_t b = i - t * B;
-    const size_t s = b / J;
-    const size_t j = b - s * J;
-    const size_t src = (static_cast<size_t>(T) * j + t) * S_ + s;
-    adv_s[i] = adv[src];
-    ret_s[i] = ret[src];
-    reset[i] = (t > 0 && done[src - S_] != 0) ? 1 : 0;
+  constexpr int kPad = 32;  // rows of a tile are one element longer
+  __shared__ float ta[256 * KE + kPad], tr[256 * KE + kPad];
+  __shared__ uint8_t td[256 * KE + kPad];
+  const int J = L / T, SB = 1 << sb;
+  const int stiles = (S - 1) / SB + 1, jtiles = (J - 1) / JB + 1;
+  const int P = SB + 1;  // odd: a column of the tile lies in 64 different banks
+  const size_t S_ = static_cast<size_t>(S), tiles = static_cast<size_t>(T) * stiles * jtiles;
+  for (size_t i = blockIdx.x; i < tiles; i += gridDim.x) {
+    const int t = static_cast<int>(i / (static_cast<size_t>(stiles) * jtiles));
+    const int rest = static_cast<int>(i - static_cast<size_t>(t) * stiles * jtiles);
+    const int s0 = rest / jtiles * SB, j0 = rest % jtiles * JB;
+    const int sn = min(SB, S - s0), jn = min(JB, J - j0);
+    float a[KE], q[KE];
+    uint8_t dn[KE];
+#pragma unroll
+    for (int k = 0; k < KE; ++k) {  // every load in flight before the first store (elements outside the tile: its first)
+      const int e = threadIdx.x + 256 * k, jj = e >> sb, ss = e & (SB - 1);
+      const bool in = jj < jn && ss < sn;
+      const size_t src = (static_cast<size_t>(T) * (j0 + (in ? jj : 0)) + t) * S_ + s0 + (in ? ss : 0);
+      a[k] = adv[src];
+      q[k] = ret[src];
+      dn[k] = done[t > 0 ? src - S_ : src];
+    }
+#pragma unroll
+    for (int k = 0; k < KE; ++k) {
+      const int e = threadIdx.x + 256 * k, jj = e >> sb, ss = e & (SB - 1);
+      if (jj < jn && ss < sn) {
+        ta[jj * P + ss] = a[k];
+        tr[jj * P + ss] = q[k];
+        td[jj * P + ss] = (t > 0 && dn[k] != 0) ? 1 : 0;
+      }
+    }
+    __syncthreads();
+    const size_t dst = (static_cast<size_t>(t) * S_ + s0) * J + j0;
+    for (unsigned e = threadIdx.x; e < static_cast<unsigned>(sn * jn); e += 256) {
+      const unsigned ss = e / jn, jj = e - ss * jn;
+      const size_t o = dst + static_cast<size_t>(ss) * J + jj;
+      const unsigned c = jj * P + ss;
+      adv_s[o] = ta[c];
+      ret_s[o] = tr[c];
+      reset[o] = td[c];
+    }
+    __syncthreads();
   }
 }
 
@@ -307,6 +375,7 @@ using namespace o5;
 static constexpr int kGaeWaveScanMaxS = 256;
 static constexpr int kGaeWaveScanLongMaxS = 4096;
 static constexpr int kGaeChunkedMaxS = 32768;
+static constexpr int kGaeWaveHeld = 4;  // steps per lane the wave scan holds in registers
 static constexpr int kGaeLaneV = 4;  // segments per lane of the large-S kernel
 
 extern "C" int o5_gae(int L, int S, const float* r, const float* v, const uint8_t* done, float gamma,
@@ -324,8 +393,9 @@ extern "C" int o5_gae(int L, int S, const float* r, const float* v, const uint8_
   ktimer_begin(kSiteGae, as_stream(stream));
   const bool chunkable = L <= kGaeChunks * kGaeChunkMax;
   if (S <= kGaeWaveScanMaxS || (!chunkable && S <= kGaeWaveScanLongMaxS)) {
-    hipLaunchKernelGGL(gae_wave_per_segment, dim3((S + 3) / 4), dim3(256), 0, as_stream(stream), L, S,
-                       r, v, done, gamma, gl, adv, ret);
+    auto kernel = L <= 64 * kGaeWaveHeld ? gae_wave_per_segment<kGaeWaveHeld> : gae_wave_per_segment<0>;
+    hipLaunchKernelGGL(kernel, dim3((S + 3) / 4), dim3(256), 0, as_stream(stream), L, S, r, v, done, gamma, gl, adv,
+                       ret);
   } else if (S < kGaeChunkedMaxS && chunkable) {
     hipLaunchKernelGGL(gae_chunked, dim3((S + 63) / 64), dim3(kGaeChunks * 64), 0, as_stream(stream), L, S, r, v,
                        done, gamma, gl, adv, ret);
@@ -353,9 +423,21 @@ extern "C" int o5_segments_to_samples(int L, int S, int T, const float* adv, con
   O5_PTR(adv_s, "adv_s");
   O5_PTR(ret_s, "ret_s");
   O5_PTR(reset, "reset");
-  const size_t total = static_cast<size_t>(L) * S;
-  const size_t blocks = std::min<size_t>((total + 255) / 256, size_t{1} << 20);
-  hipLaunchKernelGGL(segments_to_samples_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
-                     as_stream(stream), L, S, T, adv, ret, done, adv_s, ret_s, reset);
+  // Tiles of JB samples x 2^sb segments, JB whole runs of a segment where they
+  // fit: 8 elements per thread, or 2 where that leaves most of the 256 CUs
+  // without a tile (S = 130, J = T = 16: 3.6 against 7.5 us).
+  const int J = L / T;
+  const int KE = static_cast<size_t>(L) * S >= size_t{256} * 2048 ? 8 : 2;
+  const int JB = std::min(J, KE == 8 ? 32 : 8);
+  int sb = 6;
+  while ((2 << sb) * JB <= 256 * KE) ++sb;
+  const size_t tiles = static_cast<size_t>(T) * (((S - 1) >> sb) + 1) * ((J - 1) / JB + 1);
+  const dim3 grid(static_cast<unsigned>(std::min<size_t>(tiles, size_t{1} << 16)));
+  if (KE == 8)
+    hipLaunchKernelGGL(segments_to_samples_kernel<8>, grid, dim3(256), 0, as_stream(stream), L, S, T, JB, sb, adv, ret,
+                       done, adv_s, ret_s, reset);
+  else
+    hipLaunchKernelGGL(segments_to_samples_kernel<2>, grid, dim3(256), 0, as_stream(stream), L, S, T, JB, sb, adv, ret,
+                       done, adv_s, ret_s, reset);
   return check_launch("o5_segments_to_samples");
 }

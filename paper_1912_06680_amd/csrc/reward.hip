@@ -9,14 +9,17 @@
 // (Staging the 10-wide rows through LDS for 16-byte coalesced loads measured
 // slower: the block-wide barriers serialise the tiles.)
 // The normalisation needs the variance of every z before any output can be
-// written, hence three launches:
+// written, hence two launches (short calls are bound by their number: L = 256,
+// 13 games, 30.6 us with GAE and the cut when a third launch merged the
+// summaries, 27.0 without it):
 //  1. reward_stats: z per (step, game); per-block (count, mean, M2) in fp64,
-//     merged in a fixed tree order;
-//  2. reward_finalize (one block): merges the block summaries in a fixed
-//     order, merges the result into the running summary, writes it back,
-//     and stores 1 / sqrt(var + eps);
-//  3. reward_apply: recomputes z (cheaper than a round trip of z through
-//     HBM: the same 84 bytes are read either way) and writes r = z * scale.
+//     merged in a fixed order; also keeps the running summary as it was;
+//  2. reward_apply: every block merges the block summaries into that running
+//     summary, in the same fixed order (at most 24 KB from L2: 9.1 us at L = 256,
+//     1152 games, against 4.0 + 7.2 as two launches), and recomputes z
+//     (cheaper than a round trip of z through HBM: the same 84 bytes are read
+//     either way) for r = z / sqrt(var + eps); block 0 writes the new running
+//     summary.
 // 20.8 bytes move per (step, segment) against 12.4 that the operation needs
 // at least (inputs once, output once): the inputs are read twice.
 #include "common.h"
@@ -86,25 +89,52 @@ __device__ __forceinline__ void shape_game(const float* __restrict__ shaped, con
   mix_game(rho, c.tau, z);
 }
 
-// Fixed-order tree merge of one summary per thread; the result is valid in
-// thread 0.
-__device__ Summary block_merge(Summary s, Summary* lds) {
-  const int tid = threadIdx.x;
-  lds[tid] = s;
+// One sum over the block's threads, the same in every thread: a butterfly in
+// each wave, then the wave sums in order.  A fixed order, so the result is the
+// same from call to call.
+__device__ double block_sum(double v, double* lds) {
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) v += __shfl_xor(v, w, 64);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int w = kRwThreads / 2; w > 0; w >>= 1) {
-    if (tid < w) lds[tid] = merge(lds[tid], lds[tid + w]);
-    __syncthreads();
+  double s = lds[0];
+#pragma unroll
+  for (int k = 1; k < kRwThreads / 64; ++k) s += lds[k];
+  __syncthreads();
+  return s;
+}
+
+// The union of KP summaries per thread (in every thread): mean = sum n_i m_i /
+// n, M2 = sum (M2_i + n_i (m_i - mean)^2), the same moments that pairwise
+// merges give, with one division instead of two at each of eight serial levels
+// (reward_stats at 13 games: 4.0 us against 4.8).
+template <int KP>
+__device__ Summary block_merge(const Summary (&s)[KP], double* lds) {
+  double n = 0.0, nm = 0.0, m2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    n += s[k].n;
+    nm += s[k].n * s[k].mean;
   }
-  return lds[0];
+  n = block_sum(n, lds);
+  const double mean = block_sum(nm, lds) / n;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const double d = s[k].mean - mean;
+    m2 += s[k].m2 + s[k].n * d * d;
+  }
+  return Summary{n, mean, block_sum(m2, lds)};
 }
 
 __global__ void __launch_bounds__(kRwThreads) reward_stats(size_t items, const float* __restrict__ shaped,
                                                            const float* __restrict__ outcome,
                                                            const float* __restrict__ game_time, RewardConsts c,
-                                                           Summary* __restrict__ part) {
-  __shared__ Summary lds[kRwThreads];
+                                                           Summary* __restrict__ part,
+                                                           const double* __restrict__ stats,
+                                                           double* __restrict__ before) {
+  __shared__ double lds[kRwThreads / 64];
   Summary s{0.0, 0.0, 0.0};
+  if (blockIdx.x == 0 && threadIdx.x < 3) before[threadIdx.x] = stats[threadIdx.x];
   for (size_t i = static_cast<size_t>(blockIdx.x) * kRwThreads + threadIdx.x; i < items;
        i += static_cast<size_t>(gridDim.x) * kRwThreads) {
     float z[kHeroes];
@@ -119,33 +149,35 @@ __global__ void __launch_bounds__(kRwThreads) reward_stats(size_t items, const f
       const double d = z[k] - m;
       q += d * d;
     }
-    s = merge(s, Summary{static_cast<double>(kHeroes), m, q});
+    const Summary g{static_cast<double>(kHeroes), m, q};
+    s = s.n == 0.0 ? g : merge(s, g);
   }
-  const Summary b = block_merge(s, lds);
+  const Summary b = block_merge({s}, lds);
   if (threadIdx.x == 0) part[blockIdx.x] = b;
-}
-
-__global__ void __launch_bounds__(kRwThreads) reward_finalize(int nparts, const Summary* __restrict__ part,
-                                                              double* __restrict__ stats, float eps,
-                                                              float* __restrict__ scale) {
-  __shared__ Summary lds[kRwThreads];
-  Summary s{0.0, 0.0, 0.0};
-  for (int i = threadIdx.x; i < nparts; i += kRwThreads) s = merge(s, part[i]);
-  const Summary b = block_merge(s, lds);
-  if (threadIdx.x == 0) {
-    const Summary run = merge(Summary{stats[0], stats[1], stats[2]}, b);
-    stats[0] = run.n;
-    stats[1] = run.mean;
-    stats[2] = run.m2;
-    *scale = static_cast<float>(1.0 / sqrt(run.m2 / run.n + static_cast<double>(eps)));
-  }
 }
 
 __global__ void __launch_bounds__(kRwThreads) reward_apply(size_t items, const float* __restrict__ shaped,
                                                            const float* __restrict__ outcome,
                                                            const float* __restrict__ game_time, RewardConsts c,
-                                                           const float* __restrict__ scale, float* __restrict__ r) {
-  const float k = *scale;
+                                                           int nparts, const Summary* __restrict__ part,
+                                                           const double* __restrict__ before,
+                                                           double* __restrict__ stats, float eps,
+                                                           float* __restrict__ r) {
+  constexpr int kPer = kRwMaxBlocks / kRwThreads;
+  __shared__ double lds[kRwThreads / 64];
+  Summary p[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int i = threadIdx.x + q * kRwThreads;
+    p[q] = i < nparts ? part[i] : Summary{0.0, 0.0, 0.0};
+  }
+  const Summary run = merge(Summary{before[0], before[1], before[2]}, block_merge(p, lds));
+  const float k = static_cast<float>(1.0 / sqrt(run.m2 / run.n + static_cast<double>(eps)));
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    stats[0] = run.n;
+    stats[1] = run.mean;
+    stats[2] = run.m2;
+  }
   for (size_t i = static_cast<size_t>(blockIdx.x) * kRwThreads + threadIdx.x; i < items;
        i += static_cast<size_t>(gridDim.x) * kRwThreads) {
     float z[kHeroes];
@@ -157,7 +189,7 @@ __global__ void __launch_bounds__(kRwThreads) reward_apply(size_t items, const f
 }
 
 struct RewardWs {
-  size_t part, scale, total;
+  size_t part, before, total;
   int blocks;
 };
 
@@ -166,8 +198,8 @@ static RewardWs reward_ws(int L, int G) {
   const size_t items = static_cast<size_t>(L) * G;
   w.blocks = static_cast<int>(std::min<size_t>((items + kRwThreads - 1) / kRwThreads, kRwMaxBlocks));
   w.part = 0;
-  w.scale = align_up(static_cast<size_t>(w.blocks) * sizeof(Summary));
-  w.total = w.scale + align_up(sizeof(float));
+  w.before = align_up(static_cast<size_t>(w.blocks) * sizeof(Summary));
+  w.total = w.before + align_up(3 * sizeof(double));
   return w;
 }
 
@@ -213,14 +245,13 @@ extern "C" int o5_reward_process(int L, int G, const float* shaped, const float*
   const size_t items = static_cast<size_t>(L) * G;
   char* wsb = static_cast<char*>(ws);
   Summary* part = reinterpret_cast<Summary*>(wsb + w.part);
-  float* scale = reinterpret_cast<float*>(wsb + w.scale);
+  double* before = reinterpret_cast<double*>(wsb + w.before);
   hipStream_t s = as_stream(stream);
   ktimer_begin(kSiteReward, s);
   hipLaunchKernelGGL(reward_stats, dim3(w.blocks), dim3(kRwThreads), 0, s, items, shaped, outcome, game_time, c,
-                     part);
-  hipLaunchKernelGGL(reward_finalize, dim3(1), dim3(kRwThreads), 0, s, w.blocks, part, stats, hp.eps, scale);
+                     part, stats, before);
   hipLaunchKernelGGL(reward_apply, dim3(w.blocks), dim3(kRwThreads), 0, s, items, shaped, outcome, game_time, c,
-                     scale, r);
+                     w.blocks, part, before, stats, hp.eps, r);
   ktimer_end(kSiteReward, s);
   return check_launch("o5_reward_process");
 }

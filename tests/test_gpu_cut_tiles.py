@@ -1,0 +1,29 @@
+"""GPU parity: o5_segments_to_samples at the edges of its tiles, bit for bit
+against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle.gae import segments_to_samples
+from paper_1912_06680_amd import o5
+from tests.gpu_util import banner, dev, host, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,S,T", [(256, 130, 16), (70, 65, 2), (64, 1, 1), (99, 2050, 33), (3, 4097, 3), (31, 129, 1)])
+def test_segments_to_samples_tiles(L, S, T):
+    need_gpu()
+    banner(f"segments_to_samples tiles L={L} S={S} T={T}")
+    rng = np.random.Generator(np.random.PCG64(L + S))
+    adv = rng.standard_normal((L, S)).astype(np.float32)
+    ret = rng.standard_normal((L, S)).astype(np.float32)
+    done = (rng.random((L, S)) < 0.2).astype(np.uint8)
+    B = S * L // T
+    a_s = torch.empty((T, B), dtype=torch.float32, device="cuda")
+    r_s = torch.empty_like(a_s)
+    reset = torch.empty((T, B), dtype=torch.uint8, device="cuda")
+    o5.o5_segments_to_samples(L, S, T, dev(adv), dev(ret), dev(done), a_s, r_s, reset)
+    ea, er, erst = segments_to_samples(adv.astype(np.float64), ret.astype(np.float64), done, T)
+    assert np.array_equal(host(a_s), ea) and np.array_equal(host(r_s), er)
+    assert np.array_equal(reset.cpu().numpy(), erst)
