@@ -23,6 +23,20 @@ __device__ __forceinline__ float ordered_sum(int n, F&& at) {
   return s;
 }
 
+// v + p[0] + p[stride] + ..., S >= 1 terms added in that order; the loads of
+// the first Q terms are all in flight together (those from S on repeat the last
+// and are not used).
+template <int Q>
+__device__ __forceinline__ float add_parts(float v, const float* __restrict__ p, int S, size_t stride) {
+  float x[Q];
+#pragma unroll
+  for (int s = 0; s < Q; ++s) x[s] = p[min(s, S - 1) * stride];
+#pragma unroll
+  for (int s = 0; s < Q; ++s) v = s < S ? v + x[s] : v;
+  for (int s = Q; s < S; ++s) v += p[s * stride];
+  return v;
+}
+
 // part[c, n] = sum of src[r, n] over rows r in chunk c = [c*rows_per_chunk, ...).
 static __global__ void __launch_bounds__(256) colsum_chunks(int R, int N, int rows_per_chunk, const float* __restrict__ src,
                                                            float* __restrict__ part) {

@@ -91,17 +91,6 @@ __device__ __forceinline__ void store_pair(uint16_t* row, int ldh, int c, float 
   row[ldh + c] = f32_to_bf16_bits(v - bf16_bits_to_f32(hb));
 }
 
-// sum_s p[s * stride], s ascending from `v`: up to four terms' loads in flight together.
-__device__ __forceinline__ float add_parts(float v, const float* __restrict__ p, int S, size_t stride) {
-  float x[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) x[s] = p[min(s, S - 1) * stride];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) v = s < S ? v + x[s] : v;
-  for (int s = 4; s < S; ++s) v += p[s * stride];
-  return v;
-}
-
 template <int N, typename F>
 __device__ __forceinline__ void each(F f) {
 #pragma unroll
@@ -156,7 +145,7 @@ __global__ void __launch_bounds__(kUrThreads, ur_waves(CH * static_cast<int>(siz
     for (int i = 0; i < CPT; ++i) {
       const int c = t + i * kUrThreads;
       if (c < A1 && head[i] != g.kext) {
-        zs[c] = add_parts(g.bp[c], g.zpart + static_cast<size_t>(n) * A1 + c, g.S, zstride);
+        zs[c] = add_parts<4>(g.bp[c], g.zpart + static_cast<size_t>(n) * A1 + c, g.S, zstride);
       }
       if (c < A) avs[c] = g.avail != nullptr ? g.avail[static_cast<size_t>(n) * A + c] : static_cast<uint8_t>(1);
     }
@@ -164,7 +153,7 @@ __global__ void __launch_bounds__(kUrThreads, ur_waves(CH * static_cast<int>(siz
     for (int i = 0; i < DPT; ++i) {
       const int j = t + i * kUrThreads;
       if (j < d) {
-        qs[j] = add_parts(g.bq[j], g.qpart + static_cast<size_t>(n) * d + j, g.Sq, qstride);
+        qs[j] = add_parts<4>(g.bq[j], g.qpart + static_cast<size_t>(n) * d + j, g.Sq, qstride);
       }
     }
     __syncthreads();
