@@ -126,6 +126,20 @@ __global__ void __launch_bounds__(kSampleWaves * 64) gumbel_sample_rows(
 static size_t sample_ws_bytes(o5_dtype dt, int B, int H, int A1, GemmPlan* plan, int unit_nk, int unit_d,
                               UnitWs* uw, size_t* unit_off) {
   *plan = plan_gemm(dt == O5_BF16, B, A1, H, Split::kFree);
+  // (more splits than the step's in bf16, or than fit in fp32, only where the
+  // scratch stays within the static buffer: the shapes that
+  // o5_policy_sample_static takes do not shrink with a faster split)
+  const size_t unit_bytes = unit_d > 0 ? unit_ws(dt, B, H, unit_nk, unit_d, false).total : 0;
+  const auto over = [&](int splits) {
+    return align_up(static_cast<size_t>(splits) * B * A1 * 4) + align_up(unit_bytes) >
+           static_cast<size_t>(O5_STATIC_SCRATCH_BYTES);
+  };
+  if (over(plan->splits)) {
+    if (dt == O5_BF16)
+      *plan = plan_gemm(true, B, A1, H, Split::kStep);
+    else if (!over(1))
+      while (over(plan->splits)) --plan->splits;
+  }
   size_t o = align_up(static_cast<size_t>(plan->splits) * B * A1 * 4);
   *unit_off = o;
   if (unit_d > 0) {
