@@ -1,0 +1,46 @@
+"""GPU: the bf16 input gradient where W_x^T does not fit, whole, in the weight
+gradient's place and is formed a run of columns at a time; against PyTorch
+autograd in fp64 at the path's tolerance."""
+import pytest
+import torch
+
+from paper_1912_06680_amd import o5
+from tests.gpu_util import TOL_BF16, assert_close, banner, host, need_gpu, workspace
+from tests.test_gpu_lstm_step import _reference
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,B,D,H", [
+    (1, 1, 1024, 64),    # runs of 384, 384 and 256 columns
+    (2, 70, 2048, 128),  # 1472 and 576
+    (2, 70, 1024, 128),  # 960 and 64
+    (2, 70, 896, 128),   # exactly one run
+    (1, 3, 8192, 128),   # six runs of 1216 and one of 896
+])
+def test_input_gradient_by_runs_of_columns(T, B, D, H):
+    need_gpu()
+    banner(f"bf16 dx by runs T={T} B={B} D={D} H={H}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D + B)
+    et = torch.bfloat16
+
+    def rnd(*s, std=1.0):
+        return torch.randn(s, generator=g, device="cuda") * std
+
+    x, Wx, Wh = rnd(T, B, D).to(et), rnd(4 * H, D, std=D ** -0.5).to(et), rnd(4 * H, H, std=0.5 * H ** -0.5).to(et)
+    b, h0, c0 = rnd(4 * H, std=0.1), rnd(B, H, std=0.3), rnd(B, H, std=0.3)
+    reset = torch.zeros((T, B), dtype=torch.uint8, device="cuda")
+    dh, dhT, dcT = rnd(T, B, H), rnd(B, H), rnd(B, H)
+    h, c = torch.empty((T, B, H), dtype=et, device="cuda"), torch.empty((T, B, H), device="cuda")
+    gates = torch.empty((T, B, 4 * H), dtype=et, device="cuda")
+    dWx, dWh = torch.full((4 * H, D), -7.0, device="cuda"), torch.full((4 * H, H), -7.0, device="cuda")
+    db, dx = torch.full((4 * H,), -7.0, device="cuda"), torch.full((T, B, D), -7.0, dtype=et, device="cuda")
+    o5.o5_lstm_fwd(o5.O5_BF16, T, B, D, H, x, Wx, Wh, b, h0, c0, reset, h, c, gates,
+                   workspace(o5.o5_lstm_fwd_workspace_bytes(o5.O5_BF16, T, B, D, H)))
+    ws = workspace(o5.o5_lstm_bptt_workspace_bytes(o5.O5_BF16, T, B, D, H))
+    ws.fill_(0xAA)
+    o5.o5_lstm_bptt(o5.O5_BF16, T, B, D, H, x, Wx, Wh, h0, c0, reset, h, c, gates, dh, dhT, dcT, dWx, dWh, db, dx, ws)
+    ref = _reference(x, Wx, Wh, b, h0, c0, reset, dh, dhT, dcT)
+    for k, v in dict(dWx=dWx, dWh=dWh, db=db, dx=dx).items():
+        assert_close(k, host(v), host(ref[k]), TOL_BF16)

@@ -1,0 +1,24 @@
+"""CPU: workspace queries hold what the chosen kernels read and no more."""
+import pytest
+
+from paper_1912_06680_amd import o5
+
+
+def _up(n):
+    return (n + 255) // 256 * 256
+
+
+def _bptt_bf16_bytes(T, B, D, H, splits):
+    """dG, dc, the recurrent product's partial sums, bf16 h0, the bias
+    gradient's partial rows, dG^T, [x | h~]^T and W_h^T (time padded to 64)."""
+    Bp = (B + 63) // 64 * 64
+    ldt = T * Bp
+    return (_up(T * B * 4 * H * 2) + _up(B * H * 4) + _up(splits * B * H * 4) + _up(B * H * 2)
+            + _up(Bp // 32 * 4 * H * 4) + _up(4 * H * ldt * 2) + _up((D + H) * ldt * 2) + _up(4 * H * H * 2))
+
+
+@pytest.mark.parametrize("T,B,D,H", [(16, 8, 4096, 4096), (1, 1, 65536, 64), (2, 256, 16384, 4096),
+                                     (16, 2048, 4096, 4096), (16, 600, 4096, 4096), (3, 130, 1024, 64)])
+def test_bptt_bf16_transposed_input_weights_need_no_room_of_their_own(T, B, D, H):
+    got = o5.o5_lstm_bptt_workspace_bytes(o5.O5_BF16, T, B, D, H)
+    assert 0 < got <= _bptt_bf16_bytes(T, B, D, H, 8)
