@@ -597,8 +597,6 @@ static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H, bool fact) {
     // gradient (W_h^T alone holds H >= 64 of them)
     w.dx_cols = static_cast<int>(
         std::min<size_t>(D, (o - w.dGT) / (static_cast<size_t>(4) * H * sizeof(uint16_t)) / 64 * 64));
-  } else if (w.step_tile != 0) {
-    o += align_up(static_cast<size_t>(H) * 4 * H * sizeof(float));  // W_h^T
   }
   w.total = o;
   return w;
@@ -710,7 +708,13 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
   float* dbpart = reinterpret_cast<float*>(ws + w.dbpart);
   E* dGT = kBf ? reinterpret_cast<E*>(ws + w.dGT) : nullptr;
   E* XHT = kBf ? reinterpret_cast<E*>(ws + w.XHT) : nullptr;
-  E* WhT = kBf || w.step_tile != 0 ? reinterpret_cast<E*>(ws + w.WhT) : nullptr;
+  // (fp32: the output dW_h [4H][H] holds W_h^T [H][4H] until the weight
+  // gradient, the last launch but the sums, writes it)
+  E* WhT = nullptr;
+  if constexpr (kBf)
+    WhT = reinterpret_cast<E*>(ws + w.WhT);
+  else if (w.step_tile != 0)
+    WhT = dWh;
   const E* h0e;
   if constexpr (kBf) {
     E* tmp = reinterpret_cast<E*>(ws + w.h0e);

@@ -22,3 +22,12 @@ def _bptt_bf16_bytes(T, B, D, H, splits):
 def test_bptt_bf16_transposed_input_weights_need_no_room_of_their_own(T, B, D, H):
     got = o5.o5_lstm_bptt_workspace_bytes(o5.O5_BF16, T, B, D, H)
     assert 0 < got <= _bptt_bf16_bytes(T, B, D, H, 8)
+
+
+@pytest.mark.parametrize("T,B,D,H", [(16, 60, 4096, 4096), (16, 256, 4096, 4096), (2, 1000, 64, 1024), (1, 1, 64, 64)])
+def test_bptt_fp32_transposed_recurrent_weights_need_no_room(T, B, D, H):
+    """dG, dc, the recurrent product's partial sums (at most 16), and the bias
+    gradient's partial rows; W_h^T waits in the output dW_h."""
+    Bp = (B + 63) // 64 * 64
+    most = (_up(T * B * 4 * H * 4) + _up(B * H * 4) + _up(16 * B * H * 4) + _up(B * H * 4) + _up(Bp // 32 * 4 * H * 4))
+    assert 0 < o5.o5_lstm_bptt_workspace_bytes(o5.O5_F32, T, B, D, H) <= most
