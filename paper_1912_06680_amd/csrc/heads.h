@@ -72,7 +72,9 @@ struct UnitWs {
 
 // Validates the head description (loss: with the gradient outputs).
 int check_unit(const char* fn, const HeadsMeta& hm, const o5_unit_head* u, bool loss);
-UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss);
+// one_pass: the loss's rows go to unit_rows, which needs the query's partial
+// sums and, in fp32, dq and the partial sums of dWq.
+UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss, bool one_pass);
 void unit_forward(o5_dtype dt, int N, int H, int nk, const o5_unit_head& u, const void* h, char* ws, const UnitWs& w,
                   hipStream_t s);
 // The query's partial sums only (for the one-pass kernel), at q [qsplits][N][d].

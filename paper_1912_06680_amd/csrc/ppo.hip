@@ -795,7 +795,7 @@ static PpoWs ppo_ws(o5_dtype dt, int N, int H, int A1, int unit_nk = 0, int unit
   }
   w.unit = o;
   if (unit_d > 0) {
-    w.uw = unit_ws(dt, N, H, unit_nk, unit_d, true);
+    w.uw = unit_ws(dt, N, H, unit_nk, unit_d, true, w.one_pass);
     o += align_up(w.uw.total);
   }
   w.total = o;

@@ -129,7 +129,7 @@ static size_t sample_ws_bytes(o5_dtype dt, int B, int H, int A1, GemmPlan* plan,
   // (more splits than the step's in bf16, or than fit in fp32, only where the
   // scratch stays within the static buffer: the shapes that
   // o5_policy_sample_static takes do not shrink with a faster split)
-  const size_t unit_bytes = unit_d > 0 ? unit_ws(dt, B, H, unit_nk, unit_d, false).total : 0;
+  const size_t unit_bytes = unit_d > 0 ? unit_ws(dt, B, H, unit_nk, unit_d, false, false).total : 0;
   const auto over = [&](int splits) {
     return align_up(static_cast<size_t>(splits) * B * A1 * 4) + align_up(unit_bytes) >
            static_cast<size_t>(O5_STATIC_SCRATCH_BYTES);
@@ -143,7 +143,7 @@ static size_t sample_ws_bytes(o5_dtype dt, int B, int H, int A1, GemmPlan* plan,
   size_t o = align_up(static_cast<size_t>(plan->splits) * B * A1 * 4);
   *unit_off = o;
   if (unit_d > 0) {
-    *uw = unit_ws(dt, B, H, unit_nk, unit_d, false);
+    *uw = unit_ws(dt, B, H, unit_nk, unit_d, false, false);
     o += align_up(uw->total);
   }
   return o;

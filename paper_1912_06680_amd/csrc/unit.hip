@@ -155,7 +155,7 @@ int check_unit(const char* fn, const HeadsMeta& hm, const o5_unit_head* u, bool 
   return O5_OK;
 }
 
-UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss) {
+UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss, bool one_pass) {
   UnitWs w{};
   const bool bf = dt == O5_BF16;
   w.d = d;
@@ -164,19 +164,23 @@ UnitWs unit_ws(o5_dtype dt, int N, int H, int nk, int d, bool loss) {
   w.ldT = cdiv(N, kUnitT) * kUnitT;
   w.nchunks = cdiv(N, 64);
   w.wsplits = 1;
-  w.qsplits = loss ? plan_gemm(bf, N, d, H, Split::kFree).splits : 1;
+  w.qsplits = one_pass ? plan_gemm(bf, N, d, H, Split::kFree).splits : 1;
   size_t o = 0;
   w.q = o;
   o += align_up(static_cast<size_t>(w.qsplits) * N * d * 4);
-  w.zext = o;
-  o += align_up(static_cast<size_t>(N) * nk * 4);
-  if (loss) {
+  if (!one_pass) {
+    w.zext = o;
+    o += align_up(static_cast<size_t>(N) * nk * 4);
+  }
+  if (loss && !one_pass) {
     w.dzext = o;
     o += align_up(static_cast<size_t>(N) * nk * 4);
-    w.dq = o;
-    o += align_up(static_cast<size_t>(N) * d * 4);
     w.dbpart = o;
     o += align_up(static_cast<size_t>(w.nchunks) * d * 4);
+  }
+  if (loss && !(one_pass && bf)) {
+    w.dq = o;
+    o += align_up(static_cast<size_t>(N) * d * 4);
     if (bf) {
       // dWq over K = N, split so the grid has about 256 blocks
       w.wsplits = std::max(1, std::min(cdiv(256, cdiv(2 * w.dp, 256) * cdiv(H, 256)), cdiv(N, 64) / 8));

@@ -31,3 +31,28 @@ def test_bptt_fp32_transposed_recurrent_weights_need_no_room(T, B, D, H):
     Bp = (B + 63) // 64 * 64
     most = (_up(T * B * 4 * H * 4) + _up(B * H * 4) + _up(16 * B * H * 4) + _up(B * H * 4) + _up(Bp // 32 * 4 * H * 4))
     assert 0 < o5.o5_lstm_bptt_workspace_bytes(o5.O5_F32, T, B, D, H) <= most
+
+
+@pytest.mark.parametrize("dt,N,H,heads,ku,d", [
+    (o5.O5_BF16, 9600, 4096, (30, 189, 32, 4), 1, 128),
+    (o5.O5_BF16, 600, 1024, (30, 40, 4), 1, 64),
+    (o5.O5_F32, 9600, 512, (400, 30), 0, 64),
+])
+def test_unit_head_adds_what_the_one_pass_kernel_reads(dt, N, H, heads, ku, d):
+    """A unit head whose rows the one-pass kernel takes adds the query's
+    partial sums, the d column sums, in bf16 the pair's and the weights'
+    columns and their partial sums, in fp32 dq and the partial sums of dWq;
+    no logits or gradients per unit, no second copy of dq."""
+    plain = o5.o5_ppo_loss_grad_workspace_bytes(dt, N, H, heads)
+    got = o5.o5_ppo_loss_grad_workspace_bytes(dt, N, H, heads, o5.unit_head(ku, d, None, None, None))
+    dp, A1 = (d + 63) // 64 * 64, sum(heads) + 1
+    A1p = (A1 + 63) // 64 * 64
+    blocks = min(N, 1024)
+    more = 8 * N * d * 4 + 4 * (blocks + 1) * (A1 + 8 + d) + 4096
+    if dt == o5.O5_BF16:
+        tiles = -(-2 * (A1p + dp) // 256) * -(-H // 256)
+        splits = max(1, min(256 // tiles, -(-N // 32) // 8))
+        more += N * 2 * dp * 2 + H * 2 * dp * 2 + splits * 2 * (A1p + dp) * H * 4
+    else:
+        more += N * d * 4 + 16 * d * H * 4
+    assert plain < got <= plain + more
