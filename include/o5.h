@@ -92,7 +92,8 @@ const char* o5_last_error(void);
  * x        [T, B, D] dt.   Wx [4H, D] dt.   Wh [4H, H] dt.   b [4H] fp32.
  * h0, c0   [B, H] fp32, the start state of each sample.
  * reset    [T, B] uint8 or NULL (no resets): nonzero zeroes the carried
- *          state before step t of sample b.
+ *          state before step t of sample b, whatever it held (infinities
+ *          and NaN too).
  * h        out [T, B, H] dt.   c: out [T, B, H] fp32.
  * gates    out [T, B, 4H] dt, the post-activation (i, f, g, o) that
  *          o5_lstm_bptt needs; NULL for inference (nothing saved).

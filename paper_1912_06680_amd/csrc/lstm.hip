@@ -59,9 +59,9 @@ __global__ void __launch_bounds__(256) lstm_fwd_cell(int B, int H, int S, const 
       ag += p[2 * H + j];
       ao += p[3 * H + j];
     }
-    const float keep = (reset_t && reset_t[b]) ? 0.0f : 1.0f;
     const size_t hj = static_cast<size_t>(b) * H + j;
-    const float cp = keep * c_prev[hj];
+    const float cpv = c_prev[hj];
+    const float cp = (reset_t && reset_t[b]) ? 0.0f : cpv;
     const float ig = sigmoid_f(ai), fg = sigmoid_f(af), gg = tanh_f(ag), og = sigmoid_f(ao);
     const float c = fg * cp + ig * gg;
     const float h = og * tanh_f(c);
@@ -243,7 +243,9 @@ struct EpiLstmCell {
 __device__ const uint8_t kZeroFlag = 0;
 
 // Backward cell for step t.  rec: [S][B][H] partial sums of dG_{t+1} W_h (or
-// NULL at t = T-1).  dc: in = dc arriving at c_t, out = dc for c_{t-1}.
+// NULL at t = T-1).  dc: in = dc arriving at c_t, out = dc for c_{t-1}.  A
+// reset selects zeros (it does not multiply by them), so what it cuts off may
+// be infinite or NaN.
 // Block: 64 hidden units x 32 rows; each thread owns 4 consecutive units of
 // 2 rows (16-byte fp32 and 8-byte bf16 accesses) and the block writes one
 // partial column sum of dG per gate and unit for the bias gradient.
@@ -313,8 +315,8 @@ __global__ void __launch_bounds__(256) lstm_bwd_cell(
       for (int q = 1; q < NS; ++q)
         if (q < S) acc = make_float4(acc.x + recv[i][q].x, acc.y + recv[i][q].y, acc.z + recv[i][q].z,
                                      acc.w + recv[i][q].w);
-      const float k = rnb[i] ? 0.0f : 1.0f;
-      dh = make_float4(dh.x + k * acc.x, dh.y + k * acc.y, dh.z + k * acc.z, dh.w + k * acc.w);
+      if (rnb[i]) acc = f4(0.f);
+      dh = make_float4(dh.x + acc.x, dh.y + acc.y, dh.z + acc.z, dh.w + acc.w);
     }
     const float4 dcin = dcv[i];
     const float4 ig = gin[i][0];
@@ -323,7 +325,7 @@ __global__ void __launch_bounds__(256) lstm_bwd_cell(
     const float4 og = gin[i][3];
     const float4 ct = ctv[i];
     const float4 cpr = cpv[i];
-    const float keepf = rtb[i] ? 0.0f : 1.0f;
+    const bool cut = rtb[i] != 0;
     const float* dhp = &dh.x;
     const float* dcp = &dcin.x;
     const float* ip = &ig.x;
@@ -341,13 +343,13 @@ __global__ void __launch_bounds__(256) lstm_bwd_cell(
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float tc = tanh_f(cp_[q]);
-      const float cprev = keepf * pp[q];
+      const float cprev = cut ? 0.0f : pp[q];
       const float dc = dcp[q] + dhp[q] * op[q] * (1.0f - tc * tc);
       aip[q] = dc * gp[q] * ip[q] * (1.0f - ip[q]);
       afp[q] = dc * cprev * fp[q] * (1.0f - fp[q]);
       agp[q] = dc * ip[q] * (1.0f - gp[q] * gp[q]);
       aop[q] = dhp[q] * tc * op[q] * (1.0f - op[q]);
-      dcop[q] = keepf * dc * fp[q];
+      dcop[q] = cut ? 0.0f : dc * fp[q];
     }
     Vec4<float>::store(dc_out + hj, dco);
     Vec4<E>::store(dG_t + row + j, dai);

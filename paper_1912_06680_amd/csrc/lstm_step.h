@@ -379,8 +379,7 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, int 
     float p[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) p[g] = gather<Q * NW, ROWS, PITCH>(bs[g], red, sums, r, g * UNITS + uc);
-    const float keep = (reset_t != nullptr && reset_t[row] != 0) ? 0.0f : 1.0f;
-    const float cpv = keep * cp[i];
+    const float cpv = (reset_t != nullptr && reset_t[row] != 0) ? 0.0f : cp[i];
     const float ig = sigmoid_f(p[0]), fg = sigmoid_f(p[1]), gg = tanh_f(p[2]), og = sigmoid_f(p[3]);
     const float c = fg * cpv + ig * gg;
     const float h = og * tanh_f(c);
@@ -489,13 +488,12 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
       dh = dh + rec[i];
       const float ig = gin[i][0], fg = gin[i][1], gg = gin[i][2], og = gin[i][3];
       const float tc = tanh_f(ctv[i]);
-      const float keep = rt[i] ? 0.0f : 1.0f;
       const float dc = dcv[i] + dh * og * (1.0f - tc * tc);
       d[0] = dc * gg * ig * (1.0f - ig);
-      d[1] = dc * (keep * cpv[i]) * fg * (1.0f - fg);
+      d[1] = dc * (rt[i] ? 0.0f : cpv[i]) * fg * (1.0f - fg);
       d[2] = dc * ig * (1.0f - gg * gg);
       d[3] = dh * tc * og * (1.0f - og);
-      dc_out[static_cast<size_t>(b) * H + j] = keep * dc * fg;
+      dc_out[static_cast<size_t>(b) * H + j] = rt[i] ? 0.0f : dc * fg;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         dG_t[static_cast<size_t>(b) * G + g * static_cast<size_t>(H) + j] = elem<E>::from_f32(d[g]);
