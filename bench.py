@@ -67,6 +67,12 @@ def measured_traffic(kernel, path=None):
     return k["fetch_bytes_per_launch"] + k["write_bytes_per_launch"]
 
 
+def recurrent_flop(B, T, H, ld):
+    """FLOPs of one optimizer step's recurrent products: dG_{t+1} W_h for every
+    step but the last, and (ld > 0) the heads' P_t W^T of every step."""
+    return 2.0 * B * H * ((T - 1) * 4 * H + T * ld)
+
+
 # Kernel (symbol substring) behind each timed site, for the counter summary.
 # Where one symbol serves several sites the most frequent (symbol, grid)
 # group is taken: the recurrent GEMM runs T times per step.
@@ -866,11 +872,14 @@ def main():
     # the bf16 step passes the heads' gradient in factored form: the
     # recurrent product of each step t < T-1 also takes the heads' K = ld
     # columns, the last step has those alone (T launches), the loss call
-    # writes P (ld bf16 per row) instead of dh, and the cell reads no dh
+    # writes P (ld bf16 per row) instead of dh, and the cell reads no dh.
+    # (Configurations whose steps run as one launch each have no cell launches
+    # of their own: lstm_fwd_gemm and lstm_dh_gemm then hold the cell too, and
+    # no HBM rate is given for it.)
     ld = st.ld if st.bf16 else 0
     flops = {
         "lstm_fwd_gemm": 2.0 * B * 4 * H * (D + H),
-        "lstm_dh_gemm": (2.0 * B * H * ((T - 1) * (4 * H + ld) + ld) / T) if st.bf16 else 2.0 * B * H * 4 * H,
+        "lstm_dh_gemm": 0.0,  # set below, where its launches are counted
         "lstm_dw_gemm": 2.0 * 4 * H * (D + H) * T * B,
     }
     bytes_ = {
@@ -898,6 +907,8 @@ def main():
             per = tot / cnt
             k = {"ms_per_launch": round(per, 5), "launches_per_step": cnt / args.steps,
                  "ms_per_step": round(tot / args.steps, 4)}
+            if name == "lstm_dh_gemm":
+                flops[name] = recurrent_flop(B, T, H, ld) / (cnt / args.steps)
             if name in flops:
                 k["tflops"] = round(flops[name] / (per * 1e-3) / 1e12, 2)
                 k["frac_mfma_peak"] = round(k["tflops"] / PEAK_BF16_TFLOPS, 4)

@@ -738,9 +738,10 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
                                       : lstm_bwd_cell<E, 16>;
   const bool fact = P != nullptr;
   for (int t = T - 1; t >= 0 && w.step_tile != 0; --t) {
-    // small and middle batches, and fp32: one launch per step
+    // small and middle batches, and fp32: one launch per step (timed as the
+    // recurrent product, which it holds beside the cell)
     const bool last = t == T - 1;
-    ktimer_begin(kSiteLstmBwdCell, s);
+    ktimer_begin(kSiteLstmDhGemm, s);
     const int rows = w.step_tile;
     auto kernel = step::lstm_step_bwd<E, 32>;
     if constexpr (!kBf)
@@ -757,7 +758,7 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
                        fact ? nullptr : dh + t * BH, last ? dhT : nullptr, last ? dcT : dc, dc, gates + t * BG,
                        c + t * BH, t == 0 ? c0 : c + (t - 1) * BH, reset ? reset + static_cast<size_t>(t) * B : nullptr,
                        dG + t * BG, dbpart, last ? 0 : 1, dGT, w.ldt, t * w.Bp);
-    ktimer_end(kSiteLstmBwdCell, s);
+    ktimer_end(kSiteLstmDhGemm, s);
   }
   for (int t = T - 1; t >= 0 && w.step_tile == 0; --t) {
     const float* recp = nullptr;
