@@ -1,0 +1,16 @@
+"""GPU: products whose reduction is shorter than a K tile or a few of them, at
+the edges of the rules that give them a path of their own, through the pre-LSTM
+layer; bounds as for its other shapes."""
+import pytest
+
+import tests.test_gpu_gemm_tiles as tiles
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [5, 10, 15, 20, 25, 30, 35])
+@pytest.mark.parametrize("Do,D", [(64, 128), (2048, 2048)])
+def test_f32_weight_gradient_of_a_few_rows(N, Do, D):
+    """Runs of 8 k of a single K tile: 1 to 4 of them, and two tiles (35); 64 x
+    64 and 128 x 128 block tiles."""
+    tiles.test_layer_products_within_the_rounding_bound(1, N, Do, D)
