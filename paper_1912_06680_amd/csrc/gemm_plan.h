@@ -58,6 +58,12 @@ inline int k_splits(int M, int N, int K) {
 inline GemmPlan plan_gemm_kk(int M, int N, int K, int s_min, int s_max, bool tall) {
   GemmPlan best{BfTile::kDma256, s_min, 256, 256};
   const int nkt = cdiv(K, 64);
+  // One or two K tiles leave nothing to pipeline: a small grid then takes four
+  // times the blocks on 128 x 128 tiles.  A pre-LSTM layer's forward in us, 128
+  // x 128 against the tiles below: K = 64 13.6 / 15.0 (M = 600, N = 512), 15.6 /
+  // 16.8 (1025, 1024); K = 128 14.8 / 15.9 (1025, 512); K = 192 15.5 / 16.3 (600,
+  // 512) but 15.4 / 15.1 (60, 4096); K = 384 18.4 / 18.0 (600, 512).
+  if (nkt <= 2 && static_cast<long long>(cdiv(M, 256)) * cdiv(N, 256) < 64) return {BfTile::k128x128, s_min, 256, 256};
   double t_best = 1e30;
   const struct {
     int bm, bn;
