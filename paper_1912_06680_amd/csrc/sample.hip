@@ -38,7 +38,8 @@ constexpr int kSampleWaves = 4;
 __device__ const uint8_t kSampleAllAvailable = 1;
 __device__ const float kSampleNoLogit = 0.0f;
 
-template <int CPL>
+// SMAX: the split sums whose loads are issued together (any S is taken).
+template <int CPL, int SMAX>
 __global__ void __launch_bounds__(kSampleWaves * 64) gumbel_sample_rows(
     int B, int A1, int S, const float* __restrict__ zpart, const float* __restrict__ bp,
     const uint8_t* __restrict__ avail, HeadsMeta hm, const float* __restrict__ zext, int kext, uint64_t seed,
@@ -69,8 +70,9 @@ __global__ void __launch_bounds__(kSampleWaves * 64) gumbel_sample_rows(
     // every load reads a valid address; selects drop the ones not wanted
     const int ac = min(a, A1 - 1);
     // (the split sums' loads in flight together, added in the same order: a
-    // rollout step of 60 environments 92.3 -> 90.6 us, of 4096 unchanged)
-    const float v = add_parts<8>(bp[ac], zpart + static_cast<size_t>(b) * A1 + ac, S, sstride);
+    // rollout step of 60 environments 92.3 -> 90.6 us, of 4096 unchanged.
+    // Eight loads where there is one sum cost 1 to 6 us: see the launch)
+    const float v = add_parts<SMAX>(bp[ac], zpart + static_cast<size_t>(b) * A1 + ac, S, sstride);
     const bool ext = head[i] >= 0 && head[i] == kext;
     const float ze = zep[(static_cast<size_t>(b) * nke + (ext ? idx[i] : 0)) * zes];
     z[i] = ext ? ze : a < A1 ? v : 0.0f;
@@ -220,21 +222,20 @@ int policy_sample_run(o5_dtype dt, int B, int H, const HeadsMeta& hm, const void
   const int cpl = cdiv(A1, 64);
   const dim3 grid(cdiv(B, kSampleWaves)), block(kSampleWaves * 64);
   const int kext = unit ? unit->head : -1;
-  if (cpl <= 1)
-    hipLaunchKernelGGL(gumbel_sample_rows<1>, grid, block, 0, s, B, A1, plan.splits, zpart, bp, avail, hm, zext, kext,
-                       seed, counter, act, logp, value);
-  else if (cpl <= 2)
-    hipLaunchKernelGGL(gumbel_sample_rows<2>, grid, block, 0, s, B, A1, plan.splits, zpart, bp, avail, hm, zext, kext,
-                       seed, counter, act, logp, value);
-  else if (cpl <= 4)
-    hipLaunchKernelGGL(gumbel_sample_rows<4>, grid, block, 0, s, B, A1, plan.splits, zpart, bp, avail, hm, zext, kext,
-                       seed, counter, act, logp, value);
-  else if (cpl <= 8)
-    hipLaunchKernelGGL(gumbel_sample_rows<8>, grid, block, 0, s, B, A1, plan.splits, zpart, bp, avail, hm, zext, kext,
-                       seed, counter, act, logp, value);
-  else
-    hipLaunchKernelGGL(gumbel_sample_rows<16>, grid, block, 0, s, B, A1, plan.splits, zpart, bp, avail, hm, zext, kext,
-                       seed, counter, act, logp, value);
+  // up to two split sums (a short K, or rows that fill the chip) or more.  One
+  // sum, 501 logits at H = 128, the call in us with two loads against eight:
+  // 92.4 / 99.2 for 12000 rows, 23.8 / 24.5 for 60
+  auto kernel = [&](auto cpl_c) {
+    constexpr int CPL = decltype(cpl_c)::value;
+    return plan.splits <= 2 ? gumbel_sample_rows<CPL, 2> : gumbel_sample_rows<CPL, 8>;
+  };
+  auto rows = cpl <= 1   ? kernel(std::integral_constant<int, 1>{})
+              : cpl <= 2 ? kernel(std::integral_constant<int, 2>{})
+              : cpl <= 4 ? kernel(std::integral_constant<int, 4>{})
+              : cpl <= 8 ? kernel(std::integral_constant<int, 8>{})
+                         : kernel(std::integral_constant<int, 16>{});
+  hipLaunchKernelGGL(rows, grid, block, 0, s, B, A1, plan.splits, zpart, bp, avail, hm, zext, kext, seed, counter, act,
+                     logp, value);
   ktimer_end(kSiteSample, s);
   return check_launch("o5_policy_sample");
 }
