@@ -413,13 +413,20 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
     E* __restrict__ dG_t, float* __restrict__ db_part, int db_accumulate, E* __restrict__ dGT, size_t ldt, int col0) {
   constexpr int PITCH = T + 4;
   constexpr int Q = sizeof(E) == 2 ? 2 : 1;
-  constexpr int RG = NT / T;   // row groups: a thread takes rows rg EPT .. rg EPT + EPT - 1 of one column
-  constexpr int EPT = T / RG;  // rows per thread
+  // Row groups: a thread takes EPT rows of one column.  In bf16 adjacent ones,
+  // whose dG pairs up as in lstm_bwd_cell (the same column sums); in fp32 every
+  // RG-th, so that a batch smaller than the tile is spread over the groups (a
+  // tiny optimizer step, 8 rows: 259 us against 277 with adjacent rows).
+  constexpr int RG = NT / T;
+  constexpr int EPT = T / RG;
+  constexpr bool kPairs = sizeof(E) == 2;
+  constexpr int PER_SUM = kPairs ? 2 : 32 / RG;  // rows of a thread in one partial column sum
+  constexpr int SLOTS = 32 / PER_SUM;            // such sums per 32 rows
   constexpr int TP = T + 8;    // row pitch of the transposed tile (bf16)
-  static_assert(T % 32 == 0 && EPT % 2 == 0 && 4 * T <= NT, "whole rows of db_part, row pairs, a thread per sum");
+  static_assert(T % 32 == 0 && EPT % PER_SUM == 0 && 4 * T <= NT, "whole rows of db_part, whole sums, a thread per sum");
   constexpr int NST = stages<2 * T>();
   constexpr size_t SMEM = smem_bytes<T, T, NST, PITCH, Q>();
-  constexpr size_t SUMS = sizeof(float) * (T / 2) * 4 * T;  // of row pairs
+  constexpr size_t SUMS = sizeof(float) * (T / 32) * SLOTS * 4 * T;
   constexpr size_t TQ = sizeof(E) == 2 ? sizeof(uint16_t) * 4 * T * TP : 0;
   static_assert(SUMS + TQ <= SMEM, "the epilogue's arrays reuse the ring");
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
@@ -450,11 +457,12 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
   // the cell's inputs, requested before the partial sums meet
   const int jc = tid % T, rg = tid / T;
   const int j = j0 + jc;
+  auto row_of = [&](int i) { return kPairs ? rg * EPT + i : rg + i * RG; };
   float dhv[EPT], exv[EPT], dcv[EPT], ctv[EPT], cpv[EPT], gin[EPT][4];
   bool rt[EPT];
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const int bc = min(m0 + rg * EPT + i, B - 1);
+    const int bc = min(m0 + row_of(i), B - 1);
     const size_t hj = static_cast<size_t>(bc) * H + j;
     const size_t gj = static_cast<size_t>(bc) * G + j;
     dhv[i] = dh_t != nullptr ? dh_t[hj] : 0.0f;
@@ -472,15 +480,15 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
   __syncthreads();
   float rec[EPT];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) rec[i] = gather<Q * NW, T, PITCH>(0.0f, red, sums_n, rg * EPT + i, jc);
+  for (int i = 0; i < EPT; ++i) rec[i] = gather<Q * NW, T, PITCH>(0.0f, red, sums_n, row_of(i), jc);
   __syncthreads();  // the partial sums' memory is free
 
-  float* sums = reinterpret_cast<float*>(smem);             // [T / 2][4][T]
+  float* sums = reinterpret_cast<float*>(smem);             // [T / 32][SLOTS][4][T]
   uint16_t* tq = reinterpret_cast<uint16_t*>(smem + SUMS);  // [4 T][TP]
   float sd[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const int r = rg * EPT + i, b = m0 + r;
+    const int r = row_of(i), b = m0 + r;
     float d[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (b < B) {
       float dh = dhv[i];
@@ -504,10 +512,10 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
 #pragma unroll
       for (int g = 0; g < 4; ++g) tq[(g * T + jc) * TP + r] = f32_to_bf16_bits(d[g]);
     }
-    if (i & 1) {  // a row pair is done
+    if (i % PER_SUM == PER_SUM - 1) {  // the rows of a partial sum are done
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        sums[((r >> 1) * 4 + g) * T + jc] = sd[g];
+        sums[((kPairs ? r >> 1 : (r >> 5) * SLOTS + rg) * 4 + g) * T + jc] = sd[g];
         sd[g] = 0.0f;
       }
     }
@@ -519,7 +527,7 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
     for (int k = 0; k < T / 32; ++k) {
       float s = 0.0f;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) s += sums[((k * 16 + q) * 4 + g) * T + jl];
+      for (int q = 0; q < SLOTS; ++q) s += sums[((k * SLOTS + q) * 4 + g) * T + jl];
       float* p = db_part + static_cast<size_t>(m0 / 32 + k) * G + g * static_cast<size_t>(H) + j0 + jl;
       *p = db_accumulate ? *p + s : s;  // the same block owns this entry at every step
     }
