@@ -323,6 +323,9 @@ constexpr size_t smem_bytes() {
   return ring > red ? ring : red;
 }
 
+// Read (with stride 0) where there are no reset flags.
+__device__ const uint8_t kNoReset = 0;
+
 // Forward step.  Grid: cdiv(B, ROWS) * (H / 16) blocks.  S partial sums of
 // kps pieces each (bf16), or S = 0 (fp32).
 template <typename E, int ROWS>
@@ -464,6 +467,10 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
   auto row_of = [&](int i) { return kPairs ? rg * EPT + i : rg + i * RG; };
   float dhv[EPT], exv[EPT], dcv[EPT], ctv[EPT], cpv[EPT], gin[EPT][4];
   bool rt[EPT];
+  // (absent reset flags read a zero byte: behind a branch each flag's load was
+  // waited for before the next row's loads went out, 0.5 us a step)
+  const uint8_t* rtp = reset_t != nullptr ? reset_t : &kNoReset;
+  const int rts = reset_t != nullptr ? 1 : 0;
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const int bc = min(m0 + row_of(i), B - 1);
@@ -476,7 +483,7 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
     for (int g = 0; g < 4; ++g) gin[i][g] = elem<E>::to_f32(gates_t[gj + g * static_cast<size_t>(H)]);
     ctv[i] = c_t[hj];
     cpv[i] = c_prev[hj];
-    rt[i] = reset_t != nullptr && reset_t[bc] != 0;
+    rt[i] = rtp[bc * rts] != 0;
   }
   __syncthreads();  // every wave is done with its ring
   const int sums_n = Q == 1 ? NW : S;
