@@ -496,21 +496,39 @@ static inline dim3 transpose_grid(int C, long long rows) {
 //         H = 1024: 12.5 / 34 (256), 24 / 33 (400), 35 / 34 (600: 640 blocks)
 //         H = 2048: 37 / 43 (256: 512 blocks)
 //         H = 4096: 45 / 72 (60), 69 / 92 (128: 512 blocks)
-//   fp32  H = 512: 44 / 57 (B = 1024), 179 / 164 (4096: 512 tiles)
-//         H = 1024: 43 / 65 (256), 300 / 302 (2048: 512 tiles)
+//   fp32  H = 512: 42 / 55 (B = 1024), 148 / 160 (3584: 448 tiles)
+//         H = 1024: 38 / 58 (256), 261 / 296 (1792: 448 tiles)
+// Both costs grow with K = D + H alike, so the line does not move with D in
+// bf16 (four steps, D = 64 and 4096 at H = 512 to 4096: one launch 0.32 to
+// 0.94 of the time wherever it is taken).  In fp32 the four waves take K in
+// pairs of pieces, 256 k at a time; what a K that is no multiple of 256 wastes
+// moves the line down.  Two steps of 128 x 128 tiles, one launch / separate:
+//   D = 64, H = 512 (K 576 as 768)     68 / 77 (128 tiles), 102 / 98 (192), 208 / 165 (384)
+//   D = 64, H = 1024 (K 1088 as 1280)  148 / 158 (192), 249 / 263 (320), 300 / 268 (384)
+//   D = 64, H = 2048 (K 2112 as 2304)  245 / 276 (192), 409 / 469 (320), 490 / 475 (384)
 static bool step_fwd(o5_dtype dt, int B, int D, int H) {
   if (!step::offsets_fit(dtype_size(dt), B, D, H)) return false;
-  if (dt == O5_F32) return static_cast<long long>(cdiv(B, 128)) * cdiv(4 * H, 128) < 512;
+  if (dt == O5_F32) {
+    const double waste = 256.0 * cdiv(D + H, 256) / (D + H) - 1.0;
+    return static_cast<double>(cdiv(B, 128)) * cdiv(4 * H, 128) < 512.0 - 1056.0 * waste;
+  }
   return static_cast<long long>(cdiv(B, 64)) * (H / step::UNITS) <= 512;
 }
 
-// Tile (rows and units) of the backward step's launch of lstm_step.h, or 0 where the product (split over K) and the cell are launches of
-// their own.  Whole calls of 16 steps in us, one launch per step against two:
+// Tile (rows and units) of the backward step's launch of lstm_step.h, or 0
+// where the product (split over K) and the cell are launches of their own.
+// Whole calls of 16 steps in us, one launch per step against two:
 //   bf16  H = 512: 221 / 292 (B = 256), 419 / 406 (600: 304 blocks of 32 x 32)
 //         H = 1024: 284 / 382 (256: 256 blocks), 544 / 490 (400)
 //         H = 2048: 458 / 517 (128: 256 blocks), 759 / 622 (192)
 //         H = 4096: 866 / 956 (60: 256 blocks), 1430 / 1185 (96)
-// (a second round of blocks costs as much as the first).
+// (a second round of blocks costs as much as the first).  Fewer blocks than
+// CUs win there too, also with a long K, since the separate product, split
+// eight times, leaves as much of the chip idle and pays for a second launch;
+// whole calls of 4 steps:
+//         H = 512: 49 / 61 (B = 1: 16 blocks)    H = 1024: 72 / 84 (32: 32)
+//         H = 2048: 99 / 120 (1: 64), 113 / 126 (32: 64)
+//         H = 4096: 286 / 318 (1: 128), 327 / 341 (32: 128)
 //   fp32  H = 512: 296 / 242 (B = 60: 32 blocks, each with the whole K)
 //         H = 2048: 1259 / 1100 (60), 3680 / 3848 (256)
 //         H = 4096: 3581 / 3836 (60: 256 blocks), 13367 / 15008 (256)
