@@ -147,7 +147,7 @@ struct KRows2 {
 //   i < I0 : p0[k*ld0 + i]
 //   i >= I0: row k of the second source, column i - I0, where row k lives at
 //            (k < kswitch ? p1a + k*ld1 : p1b + (k - kswitch)*ld1), zeroed when
-//            mask1[k] != 0.
+//            mask1[k] != 0 (fp32 only; the bf16 engines take no mask).
 // This expresses [x | h~_prev] over the flattened (t, b) rows, where the
 // previous hidden state of row (t, b) is h0[b] for t = 0 and h[t-1, b] after.
 template <typename E>
@@ -160,9 +160,6 @@ struct ICols2 {
   const uint8_t* mask1;
   int ld0, ld1, I0, I, K, kswitch;
 
-  __device__ __forceinline__ const E* row1(int k) const {
-    return k < kswitch ? p1a + static_cast<size_t>(k) * ld1 : p1b + static_cast<size_t>(k - kswitch) * ld1;
-  }
   // Per-thread state of the bf16 engine for a ROWS x 64 tile: the tile holds
   // (ROWS/8) x 8 blocks of 8 i x 8 k; thread t loads block (i-chunk t >> 3,
   // k-chunk t & 7) (+ NT/8 i-chunks per extra block), i.e. 8 rows k of 8
@@ -197,24 +194,6 @@ struct ICols2 {
         if ((flags & 1u) == 0u) return;  // idle or out-of-range block: store() skips it too
       }
       const int kb = k0 + kc;  // first of this thread's 8 rows k
-      // reset mask of the 8 rows (applies to the second source only)
-      uint32_t mlo = 0, mhi = 0;
-      if (l.mask1 != nullptr) {
-        if (kb + 8 <= l.K) {
-          const uint2 m = *reinterpret_cast<const uint2*>(l.mask1 + kb);
-          mlo = m.x;
-          mhi = m.y;
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const uint32_t b = (kb + j < l.K) ? l.mask1[kb + j] : 0u;
-            if (j < 4)
-              mlo |= b << (8 * j);
-            else
-              mhi |= b << (8 * (j - 4));
-          }
-        }
-      }
 #pragma unroll
       for (int u = 0; u < kPer; ++u) {
         const bool ok = (flags >> u) & 1u;
@@ -231,9 +210,7 @@ struct ICols2 {
             p = (kk < l.kswitch ? l.p1a + static_cast<size_t>(kk) * l.ld1
                                 : l.p1b + static_cast<size_t>(kk - l.kswitch) * l.ld1) + col[u];
           }
-          const uint32_t mb = (j < 4 ? mlo >> (8 * j) : mhi >> (8 * (j - 4))) & 0xffu;
-          const bool keep = ok && kin && !(second && mb != 0u);
-          r[u * 8 + j] = sel4(keep, *reinterpret_cast<const uint4*>(p));
+          r[u * 8 + j] = sel4(ok && kin, *reinterpret_cast<const uint4*>(p));
         }
       }
     }
@@ -511,28 +488,22 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 1)
 
 // ------------------------------------------------------------ launchers
 
-// Tile configurations of the bf16 engines: block tile, waves (x 64 threads).
-//   kDma256    256 x 256, 8 waves, buffer loads straight to LDS (gemm_kk.h for
-//              two K-contiguous operands, else gemm_dma.h)
-//   k256x256w8 256 x 256, 8 waves of 128 x 64, register-staged (operands the
-//              direct-to-LDS engines cannot take: a masked second source)
-//   k128x128   128 x 128, 4 waves of 64 x 64, register-staged (small grids)
-enum class BfTile { kDma256, k256x256w8, k128x128 };
+// Engines of the bf16 products.
+//   kDma256   256 x 256 tiles (or gemm_kk.h's other shapes), buffer loads
+//             straight to LDS: gemm_kk.h for two K-contiguous operands within
+//             32-bit offsets, else gemm_dma.h
+//   k128x128  128 x 128 tiles, 4 waves of 64 x 64, register-staged: small grids
+//             with an I-contiguous operand, or with one or two K tiles
+enum class BfTile { kDma256, k128x128 };
 
 template <class AL, class BL, class Epi>
 inline void launch_gemm_bf16(const AL& al, const BL& bl, const Epi& epi, int M, int N, int K, int splits,
-                             BfTile tile, hipStream_t s) {
+                             hipStream_t s) {
   const int nkt = (K + 63) / 64;
   const int kps = (nkt + splits - 1) / splits;
-  if (tile == BfTile::k256x256w8) {
-    const unsigned tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    hipLaunchKernelGGL((gemm_bf16_mfma<256, 256, 128, 64, AL, BL, Epi>), dim3(tiles, 1, splits), dim3(512), 0, s,
-                       al, bl, epi, M, N, K, kps);
-  } else {
-    const unsigned tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    hipLaunchKernelGGL((gemm_bf16_mfma<128, 128, 64, 64, AL, BL, Epi>), dim3(tiles, 1, splits), dim3(256), 0, s, al,
-                       bl, epi, M, N, K, kps);
-  }
+  const unsigned tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  hipLaunchKernelGGL((gemm_bf16_mfma<128, 128, 64, 64, AL, BL, Epi>), dim3(tiles, 1, splits), dim3(256), 0, s, al, bl,
+                     epi, M, N, K, kps);
 }
 
 }  // namespace o5

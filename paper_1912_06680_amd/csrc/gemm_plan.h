@@ -54,8 +54,12 @@ inline int k_splits(int M, int N, int K) {
 // bytes) and 2.1 on 320 x 256.  (A 128 x 128 register-staged tile takes as
 // long for a K tile of a quarter of the products: M = 600, N = 4096, K =
 // 16384 took 202 us on it and takes 80 as 32 tiles of 320 x 256 in eight
-// splits.)  tall: 320-row tiles allowed (not with the LSTM cell's epilogue).
-inline GemmPlan plan_gemm_kk(int M, int N, int K, int s_min, int s_max, bool tall) {
+// splits.)  Products of a few dozen columns follow the same estimate: whole
+// calls over 75 logits in us, on 128 x 128 tiles or one fixed 256-wide tile
+// and with the choice, H = 4096: sampler (splits freely) 21.8 / 18.3 for 60
+// rows, 32.2 / 26.0 for 4096, 61.0 / 49.2 for 12000; loss (the step's split)
+// 77.4 / 71.4 for 600 rows, 153 / 137 for 9600.
+inline GemmPlan plan_gemm_kk(int M, int N, int K, int s_min, int s_max) {
   GemmPlan best{BfTile::kDma256, s_min, 256, 256};
   const int nkt = cdiv(K, 64);
   // One or two K tiles leave nothing to pipeline: a small grid then takes four
@@ -69,16 +73,16 @@ inline GemmPlan plan_gemm_kk(int M, int N, int K, int s_min, int s_max, bool tal
     int bm, bn;
     double per_tile;
   } shapes[3] = {{256, 256, 1.75}, {256, 128, 1.1}, {320, 256, 2.1}};
-  for (int i = 0; i < (tall ? 3 : 2); ++i) {
-    const long long tiles = static_cast<long long>(cdiv(M, shapes[i].bm)) * cdiv(N, shapes[i].bn);
+  for (const auto& sh : shapes) {
+    const long long tiles = static_cast<long long>(cdiv(M, sh.bm)) * cdiv(N, sh.bn);
     for (int s = s_min; s <= s_max && (s == s_min || nkt / s >= 4); ++s) {
       const double rounds = static_cast<double>((tiles * s + 255) / 256);
       const double bytes = 4.0 * s * M * N;
       const double t =
-          rounds * (cdiv(nkt, s) * shapes[i].per_tile + 5.0) + bytes / 2.2e6 + (s > 1 ? bytes / 4.5e6 : 0.0);
+          rounds * (cdiv(nkt, s) * sh.per_tile + 5.0) + bytes / 2.2e6 + (s > 1 ? bytes / 4.5e6 : 0.0);
       if (t < t_best) {
         t_best = t;
-        best = {BfTile::kDma256, s, shapes[i].bm, shapes[i].bn};
+        best = {BfTile::kDma256, s, sh.bm, sh.bn};
       }
     }
   }
@@ -88,10 +92,10 @@ inline GemmPlan plan_gemm_kk(int M, int N, int K, int s_min, int s_max, bool tal
 // A product of K-contiguous operands (KRows2) in either type: split as the
 // optimizer step's, unsplit, or split as is fastest.
 enum class Split { kStep, kOne, kFree };
-inline GemmPlan plan_gemm(bool bf16, int M, int N, int K, Split split, bool tall = true) {
+inline GemmPlan plan_gemm(bool bf16, int M, int N, int K, Split split) {
   if (bf16) {
     const int s = split == Split::kStep ? k_splits(M, N, K) : 1;
-    return plan_gemm_kk(M, N, K, s, split == Split::kFree ? 8 : s, tall);
+    return plan_gemm_kk(M, N, K, s, split == Split::kFree ? 8 : s);
   }
   GemmPlan p = plan_gemm_f32(M, N, K);
   if (split == Split::kOne) p.splits = 1;
@@ -104,12 +108,6 @@ inline GemmPlan plan_gemm_icols(bool bf16, int M, int N) {
   const long long t256 = static_cast<long long>(cdiv(M, 256)) * cdiv(N, 256);
   return {bf16 && t256 < 64 ? BfTile::k128x128 : BfTile::kDma256, 1, 256, 256};
 }
-
-// The direct-to-LDS engine takes I-contiguous operands without a mask only.
-template <class L>
-inline bool dma_ok(const L&) { return true; }
-template <typename E>
-inline bool dma_ok(const ICols2<E>& l) { return l.mask1 == nullptr; }
 
 template <class AL, class BL, class Epi>
 inline void run_gemm(const GemmPlan& p, const AL& al, const BL& bl, const Epi& epi, int M, int N, int K,
@@ -127,10 +125,10 @@ inline void run_gemm(const GemmPlan& p, const AL& al, const BL& bl, const Epi& e
         return;
       }
     }
-    if (p.tile == BfTile::kDma256 && dma_ok(al) && dma_ok(bl))
+    if (p.tile == BfTile::kDma256)
       launch_gemm_bf16_dma(al, bl, epi, M, N, K, p.splits, s);
     else
-      launch_gemm_bf16(al, bl, epi, M, N, K, p.splits, p.tile == BfTile::kDma256 ? BfTile::k256x256w8 : p.tile, s);
+      launch_gemm_bf16(al, bl, epi, M, N, K, p.splits, s);
   } else {
     launch_gemm_f32(al, bl, epi, M, N, K, p.splits, s);
   }
