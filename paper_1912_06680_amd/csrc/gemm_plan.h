@@ -25,7 +25,7 @@ inline GemmPlan plan_gemm_f32(int M, int N, int K) {
   return {BfTile::kDma256, std::max(1, std::min(s, 16)), 256, 256};
 }
 
-// K split of the products on the optimizer step's path in bf16.  A partial sum
+// K split of the LSTM's and the loss's products in bf16.  A partial sum
 // ends where a split ends, so the split decides the rounding of h, the gates
 // and dG; a step's results over several updates amplify a difference there
 // (Adam's first updates take the sign of gradients near zero), so it is a

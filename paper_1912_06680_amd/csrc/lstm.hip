@@ -578,16 +578,17 @@ struct BwdWs {
   GemmPlan plan_dh, plan_dw, plan_dx;
 };
 
-static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H, bool fact) {
+static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H) {
   BwdWs w;
   const bool bf = dt == O5_BF16;
   w.Bp = time_pad(B);
   w.nbc = w.Bp / kPwRows;  // cell row blocks; those past B only write zeros
   w.ldt = static_cast<size_t>(T) * w.Bp;
-  // (the workspace query serves both backward calls: partial sums for the
-  // larger split of the two)
-  w.plan_dh = plan_gemm(bf, B, H, 4 * H, fact ? Split::kStep : Split::kFree);
-  const int most = std::max(plan_gemm(bf, B, H, 4 * H, Split::kStep).splits, plan_gemm(bf, B, H, 4 * H, Split::kFree).splits);
+  // (split as the optimizer step's in both backward calls: dG is rounded to
+  // bf16 behind these sums, so a split of its own would change an unfactored
+  // call's bits with the path; split freely, T = 16, B = 600, D = H = 4096 takes
+  // 3901 us against 4211)
+  w.plan_dh = plan_gemm(bf, B, H, 4 * H, Split::kStep);
   // dW and dx are written directly (M x N tiles are plentiful)
   w.plan_dw = plan_gemm(bf, 4 * H, D + H, bf ? static_cast<int>(w.ldt) : T * B, Split::kOne);
   w.plan_dx = plan_gemm(bf, T * B, D, 4 * H, Split::kOne);
@@ -598,7 +599,7 @@ static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H, bool fact) {
   o += align_up(static_cast<size_t>(B) * H * sizeof(float));
   w.rec = o;
   w.step_tile = step_bwd_tile(dt, B, D, H);
-  if (w.step_tile == 0) o += align_up(static_cast<size_t>(most) * B * H * sizeof(float));
+  if (w.step_tile == 0) o += align_up(static_cast<size_t>(w.plan_dh.splits) * B * H * sizeof(float));
   w.h0e = o;
   o += align_up(static_cast<size_t>(B) * H * dtype_size(dt));
   w.dbpart = o;
@@ -764,10 +765,10 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
     auto kernel = step::lstm_step_bwd<E, 32>;
     if constexpr (!kBf)
       if (rows == 64) kernel = step::lstm_step_bwd<E, 64>;
-    // the partial sums: the factored call's as its separate product would
-    // take them (one over P alone at the last step), else one per wave
+    // the partial sums as the separate product takes them (at the last step
+    // one: over P alone, or none of anything)
     const int nk = ((fact ? ldp : 0) + (last ? 0 : 4 * H)) / 64;
-    const int S = !kBf ? 0 : !fact ? step::NW : last ? 1 : w.plan_dh.splits;
+    const int S = !kBf ? 0 : last ? 1 : w.plan_dh.splits;
     hipLaunchKernelGGL(kernel, dim3((w.Bp / rows) * (H / rows)), dim3(step::NT), 0, s, B, w.Bp, H, S,
                        S ? cdiv(nk, S) : 0,
                        fact ? P + static_cast<size_t>(t) * B * ldp : nullptr, Wf, fact ? ldp : 0,
@@ -927,14 +928,14 @@ extern "C" int o5_lstm_fwd(o5_dtype dt, int T, int B, int D, int H, const void* 
 
 extern "C" size_t o5_lstm_bptt_workspace_bytes(o5_dtype dt, int T, int B, int D, int H) {
   if (check_dims("o5_lstm_bptt_workspace_bytes", dt, T, B, D, H) != O5_OK) return 0;
-  return bwd_ws(dt, T, B, D, H, false).total;
+  return bwd_ws(dt, T, B, D, H).total;
 }
 
 // Validation shared by the two backward calls (all but the heads' gradient).
 static int bptt_check(const char* fn, o5_dtype dt, int T, int B, int D, int H, const void* x, const void* Wx,
                       const void* Wh, const float* h0, const float* c0, const uint8_t* reset, const void* h,
                       const float* c, const void* gates, const float* dhT, const float* dcT, float* dWx, float* dWh,
-                      float* db, void* dx, void* ws, size_t ws_bytes, bool fact, BwdWs* w) {
+                      float* db, void* dx, void* ws, size_t ws_bytes, BwdWs* w) {
   int st = check_dims(fn, dt, T, B, D, H);
   if (st != O5_OK) return st;
   O5_PTR_IN(fn, x, "x");
@@ -952,7 +953,7 @@ static int bptt_check(const char* fn, o5_dtype dt, int T, int B, int D, int H, c
   O5_PTR_IN(fn, dWh, "dWh");
   O5_PTR_IN(fn, db, "db");
   O5_OPT_PTR_IN(fn, dx, "dx");
-  *w = bwd_ws(dt, T, B, D, H, fact);
+  *w = bwd_ws(dt, T, B, D, H);
   O5_CHECK(ws != nullptr && ws_bytes >= w->total, O5_E_WORKSPACE, "%s: workspace needs %zu bytes, got %zu", fn,
            w->total, ws ? ws_bytes : static_cast<size_t>(0));
   O5_CHECK(aligned16(ws), O5_E_ALIGN, "%s: ws is not 16-byte aligned", fn);
@@ -965,7 +966,7 @@ extern "C" int o5_lstm_bptt(o5_dtype dt, int T, int B, int D, int H, const void*
                             float* dWh, float* db, void* dx, void* ws, size_t ws_bytes, void* stream) {
   BwdWs w;
   const int st = bptt_check("o5_lstm_bptt", dt, T, B, D, H, x, Wx, Wh, h0, c0, reset, h, c, gates, dhT, dcT, dWx,
-                            dWh, db, dx, ws, ws_bytes, false, &w);
+                            dWh, db, dx, ws, ws_bytes, &w);
   if (st != O5_OK) return st;
   O5_PTR(dh, "dh");
   char* wsp = static_cast<char*>(ws);
@@ -990,7 +991,7 @@ extern "C" int o5_lstm_bptt_factored(o5_dtype dt, int T, int B, int D, int H, co
            static_cast<int>(dt));
   BwdWs w;
   const int st = bptt_check("o5_lstm_bptt_factored", dt, T, B, D, H, x, Wx, Wh, h0, c0, reset, h, c, gates, dhT,
-                            dcT, dWx, dWh, db, dx, ws, ws_bytes, true, &w);
+                            dcT, dWx, dWh, db, dx, ws, ws_bytes, &w);
   if (st != O5_OK) return st;
   O5_CHECK(ld >= 64 && ld % 64 == 0 && ld <= 4096, O5_E_SHAPE,
            "o5_lstm_bptt_factored: ld=%d must be a multiple of 64 in 64..4096", ld);

@@ -32,10 +32,10 @@ def test_forward_step_with_more_sums_than_waves(T, B, D, H):
     check(True, T, B, D, H)
 
 
-def _bits(T, D, H, small, large, factored):
+def _bits(T, D, H, small, large, backward):
     """Outputs of `large` samples, and of their first `small` alone."""
     need_gpu()
-    banner(f"bits on both paths B={small} and {large} D={D} H={H} factored={factored}")
+    banner(f"bits on both paths B={small} and {large} D={D} H={H} backward={backward}")
     et, dt, ld = torch.bfloat16, o5.O5_BF16, 256
     g = torch.Generator(device="cuda")
     g.manual_seed(H + large)
@@ -46,22 +46,27 @@ def _bits(T, D, H, small, large, factored):
     x, Wx, Wh = rnd(T, large, D).to(et), rnd(4 * H, D, std=D ** -0.5).to(et), rnd(4 * H, H, std=0.5 * H ** -0.5).to(et)
     b, h0, c0 = rnd(4 * H, std=0.1), rnd(large, H, std=0.3), rnd(large, H, std=0.3)
     P, W = rnd(T, large, ld, std=0.1).to(et), rnd(H, ld, std=0.1).to(et)
+    dh = rnd(T, large, H)
     reset = (torch.rand((T, large), generator=g, device="cuda") < 0.1).to(torch.uint8)
     out = []
     for B in (large, small):
-        xs, rs, Ps = (v[:, :B].contiguous() for v in (x, reset, P))
+        xs, rs, Ps, dhs = (v[:, :B].contiguous() for v in (x, reset, P, dh))
         hs, cs = h0[:B].contiguous(), c0[:B].contiguous()
         h, c = torch.empty((T, B, H), dtype=et, device="cuda"), torch.empty((T, B, H), device="cuda")
         gates = torch.empty((T, B, 4 * H), dtype=et, device="cuda")
         o5.o5_lstm_fwd(dt, T, B, D, H, xs, Wx, Wh, b, hs, cs, rs, h, c, gates,
                        workspace(o5.o5_lstm_fwd_workspace_bytes(dt, T, B, D, H)))
         got = dict(h=h, c=c, gates=gates)
-        if factored:
+        if backward:
             dx = torch.empty((T, B, D), dtype=et, device="cuda")
-            o5.o5_lstm_bptt_factored(dt, T, B, D, H, xs, Wx, Wh, hs, cs, rs, h, c, gates, Ps.view(T * B, ld), W, ld, None,
-                                     None, torch.empty((4 * H, D), device="cuda"), torch.empty((4 * H, H), device="cuda"),
-                                     torch.empty(4 * H, device="cuda"), dx,
-                                     workspace(o5.o5_lstm_bptt_workspace_bytes(dt, T, B, D, H)))
+            grads = (torch.empty((4 * H, D), device="cuda"), torch.empty((4 * H, H), device="cuda"),
+                     torch.empty(4 * H, device="cuda"), dx)
+            ws = workspace(o5.o5_lstm_bptt_workspace_bytes(dt, T, B, D, H))
+            if backward == "factored":
+                o5.o5_lstm_bptt_factored(dt, T, B, D, H, xs, Wx, Wh, hs, cs, rs, h, c, gates, Ps.view(T * B, ld), W, ld,
+                                         None, None, *grads, ws)
+            else:
+                o5.o5_lstm_bptt(dt, T, B, D, H, xs, Wx, Wh, hs, cs, rs, h, c, gates, dhs, None, None, *grads, ws)
             got["dx"] = dx
         out.append(got)
     for k in out[0]:
@@ -71,10 +76,11 @@ def _bits(T, D, H, small, large, factored):
 def test_forward_bits_do_not_depend_on_the_path():
     """512 samples take one launch per step (512 blocks), 576 the product, split
     in two for both batches, and the cell."""
-    _bits(3, 64, 1024, 512, 576, False)
+    _bits(3, 64, 1024, 512, 576, None)
 
 
-def test_factored_backward_bits_do_not_depend_on_the_path():
+@pytest.mark.parametrize("backward", ["factored", "plain"])
+def test_backward_bits_do_not_depend_on_the_path(backward):
     """256 samples take one launch per backward step (256 blocks), 320 the
     product, split in eight for both batches, and the cell; dx holds dG's bits."""
-    _bits(3, 64, 1024, 256, 320, True)
+    _bits(3, 64, 1024, 256, 320, backward)
