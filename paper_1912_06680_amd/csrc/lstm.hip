@@ -14,8 +14,8 @@
 //   cell  dh = dh_heads[t] + (1 - reset[t+1]) R;  dG_t and the carried dc;
 //         per-block column sums of dG_t for the bias gradient
 // then once:
-//   GEMM  [dW_x | dW_h] = dG^T . [x | h~_prev]             (M = 4H, N = D + H, K = T B)
 //   GEMM  dx = dG . W_x                                     (M = T B, N = D, K = 4H), optional
+//   GEMM  [dW_x | dW_h] = dG^T . [x | h~_prev]             (M = 4H, N = D + H, K = T B)
 //   db    = fixed-order sum of the per-block column sums.
 //
 // Small and middle batches (bf16) and most fp32 shapes take each step, product
@@ -574,7 +574,6 @@ struct BwdWs {
   int step_tile;  // tile of the one-launch backward step, or 0
   int Bp;       // B rounded up to the cell's row block (bf16 path: time-padded K of dW)
   size_t ldt;   // T * Bp, the leading dimension of dGT and XHT
-  int dx_cols;  // columns of W_x whose transpose fits there at a time (bf16 input gradient)
   GemmPlan plan_dh, plan_dw, plan_dx;
 };
 
@@ -613,11 +612,6 @@ static BwdWs bwd_ws(o5_dtype dt, int T, int B, int D, int H) {
     o += align_up(static_cast<size_t>(D + H) * w.ldt * sizeof(uint16_t));
     w.WhT = o;
     o += align_up(static_cast<size_t>(H) * 4 * H * sizeof(uint16_t));
-    // Once the weight gradient is done dG^T, [x | h~]^T and W_h^T are read no
-    // more: columns of W_x transposed, [.][4H], take their place for the input
-    // gradient (W_h^T alone holds H >= 64 of them)
-    w.dx_cols = static_cast<int>(
-        std::min<size_t>(D, (o - w.dGT) / (static_cast<size_t>(4) * H * sizeof(uint16_t)) / 64 * 64));
   }
   w.total = o;
   return w;
@@ -829,6 +823,29 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
                        w.ldt, t * w.Bp);
     ktimer_end(kSiteLstmBwdCell, s);
   }
+  if (dx) {
+    // dx = dG . W_x :  A(i=r, k=n) = dG[r, n];  B(j=d, k=n) = W_x[n, d]
+    const int R = T * B;
+    KRows2<E> al{dG, nullptr, nullptr, 4 * H, 0, 4 * H, 4 * H, R};
+    EpiStoreElem<E> epi{dx, D};
+    ktimer_begin(kSiteLstmDxGemm, s);
+    if constexpr (kBf) {
+      // against W_x^T [D][4H], which waits in the output dW_x until the weight
+      // gradient below writes that: with both operands K-contiguous the
+      // product runs on gemm_kk (T B = 9600, D = H = 4096: 1035 + 47 us with
+      // the transposition against 1784 us on an I-contiguous W_x; T B = 1, D =
+      // 2048, H = 1024, the whole call: 84 against 135)
+      E* WxT = reinterpret_cast<E*>(dWx);
+      hipLaunchKernelGGL(transpose_rows<E>, transpose_grid(D, 4 * H), dim3(256), 0, s, 1, 4 * H, 4 * H, D, Wx, Wx,
+                         4 * H, D, nullptr, WxT, static_cast<size_t>(4 * H));
+      KRows2<E> bl{WxT, nullptr, nullptr, 4 * H, 0, 4 * H, 4 * H, D};
+      run_gemm(w.plan_dx, al, bl, epi, R, D, 4 * H, s);
+    } else {
+      ICols2<E> bl{Wx, nullptr, nullptr, nullptr, D, 0, D, D, 4 * H, 0};
+      run_gemm(w.plan_dx, al, bl, epi, R, D, 4 * H, s);
+    }
+    ktimer_end(kSiteLstmDxGemm, s);
+  }
   // [dW_x | dW_h] = dG^T . [x | h~_prev] over the T*B rows r = t*B + b
   {
     EpiStoreF32Split2 epi{dWx, dWh, D, H, D};
@@ -855,31 +872,6 @@ static int lstm_bptt_impl(int T, int B, int D, int H, const E* x, const E* Wx, c
     }
   }
   hipLaunchKernelGGL(colsum_rows4, dim3(cdiv(4 * H, 64)), dim3(256), 0, s, w.nbc, 4 * H, dbpart, db);
-  if (dx) {
-    // dx = dG . W_x :  A(i=r, k=n) = dG[r, n];  B(j=d, k=n) = W_x[n, d]
-    const int R = T * B;
-    KRows2<E> al{dG, nullptr, nullptr, 4 * H, 0, 4 * H, 4 * H, R};
-    ktimer_begin(kSiteLstmDxGemm, s);
-    if constexpr (kBf) {
-      // W_x^T takes the place of the weight gradient's operands, a run of
-      // dx_cols columns of W_x at a time: with both operands K-contiguous the
-      // product runs on gemm_kk (T B = 9600, D = H = 4096: 1035 + 47 us with
-      // the transposition against 1784 us on an I-contiguous W_x)
-      E* WxT = dGT;
-      for (int d0 = 0; d0 < D; d0 += w.dx_cols) {
-        const int n = std::min(w.dx_cols, D - d0);
-        hipLaunchKernelGGL(transpose_rows<E>, transpose_grid(n, 4 * H), dim3(256), 0, s, 1, 4 * H, 4 * H, n, Wx + d0,
-                           Wx + d0, 4 * H, D, nullptr, WxT, static_cast<size_t>(4 * H));
-        KRows2<E> bl{WxT, nullptr, nullptr, 4 * H, 0, 4 * H, 4 * H, n};
-        run_gemm(n == D ? w.plan_dx : plan_gemm(true, R, n, 4 * H, Split::kOne), al, bl, EpiStoreElem<E>{dx + d0, D},
-                 R, n, 4 * H, s);
-      }
-    } else {
-      ICols2<E> bl{Wx, nullptr, nullptr, nullptr, D, 0, D, D, 4 * H, 0};
-      run_gemm(w.plan_dx, al, bl, EpiStoreElem<E>{dx, D}, R, D, 4 * H, s);
-    }
-    ktimer_end(kSiteLstmDxGemm, s);
-  }
   return check_launch("o5_lstm_bptt");
 }
 
