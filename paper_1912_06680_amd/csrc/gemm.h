@@ -6,6 +6,7 @@
 //   backward dh    = dG_t . W_h                             (B I-contiguous)
 //   weights  dW    = dG^T . [x | h~_prev]                   (A, B I-contiguous)
 //   input    dx    = dG . W_x                               (B I-contiguous)
+// (as stored; the bf16 path transposes the I-contiguous ones beforehand)
 // A loader reports whether its reduction index k is the contiguous one
 // (kKMajor) and, for the bf16 engine, has a per-thread Tile state that
 // precomputes everything that does not change along K (row offsets, masks,

@@ -492,12 +492,12 @@ static inline dim3 transpose_grid(int C, long long rows) {
 // product's with its 256 x 256 (bf16) or 128 x 128 (fp32) tiles, which reuse
 // operands better but need a grid that fills the chip.  us per step, one
 // launch against product and cell, D = H:
-//   bf16  H = 512: 18 / 27 (B = 600), 19 / 31 (1024: 512 blocks)
-//         H = 1024: 12.5 / 34 (256), 24 / 33 (400), 35 / 34 (600: 640 blocks)
-//         H = 2048: 37 / 43 (256: 512 blocks)
-//         H = 4096: 45 / 72 (60), 69 / 92 (128: 512 blocks)
-//   fp32  H = 512: 42 / 55 (B = 1024), 148 / 160 (3584: 448 tiles)
-//         H = 1024: 38 / 58 (256), 261 / 296 (1792: 448 tiles)
+//   bf16  H = 512: 18 / 27 (B = 600), 19 / 30 (1024: 512 blocks)
+//         H = 1024: 13 / 34 (256), 24 / 33 (400), 35 / 33 (600: 640 blocks)
+//         H = 2048: 38 / 43 (256: 512 blocks)
+//         H = 4096: 45 / 73 (60), 71 / 90 (128: 512 blocks)
+//   fp32  H = 512: 45 / 57 (B = 1024), 162 / 166 (3584: 448 tiles)
+//         H = 1024: 40 / 59 (256), 271 / 301 (1792: 448 tiles)
 // Both costs grow with K = D + H alike, so the line does not move with D in
 // bf16 (four steps, D = 64 and 4096 at H = 512 to 4096: one launch 0.32 to
 // 0.94 of the time wherever it is taken).  In fp32 the four waves take K in
@@ -518,20 +518,20 @@ static bool step_fwd(o5_dtype dt, int B, int D, int H) {
 // Tile (rows and units) of the backward step's launch of lstm_step.h, or 0
 // where the product (split over K) and the cell are launches of their own.
 // Whole calls of 16 steps in us, one launch per step against two:
-//   bf16  H = 512: 221 / 292 (B = 256), 419 / 406 (600: 304 blocks of 32 x 32)
-//         H = 1024: 284 / 382 (256: 256 blocks), 544 / 490 (400)
-//         H = 2048: 458 / 517 (128: 256 blocks), 759 / 622 (192)
-//         H = 4096: 866 / 956 (60: 256 blocks), 1430 / 1185 (96)
+//   bf16  H = 512: 210 / 313 (B = 256), 407 / 409 (600: 304 blocks of 32 x 32)
+//         H = 1024: 282 / 385 (256: 256 blocks), 508 / 492 (400)
+//         H = 2048: 444 / 529 (128: 256 blocks), 718 / 610 (192)
+//         H = 4096: 846 / 974 (60: 256 blocks), 1401 / 1182 (96)
 // (a second round of blocks costs as much as the first).  Fewer blocks than
 // CUs win there too, also with a long K, since the separate product, split
 // eight times, leaves as much of the chip idle and pays for a second launch;
 // whole calls of 4 steps:
-//         H = 512: 49 / 61 (B = 1: 16 blocks)    H = 1024: 72 / 84 (32: 32)
-//         H = 2048: 99 / 120 (1: 64), 113 / 126 (32: 64)
-//         H = 4096: 286 / 318 (1: 128), 327 / 341 (32: 128)
-//   fp32  H = 512: 296 / 242 (B = 60: 32 blocks, each with the whole K)
-//         H = 2048: 1259 / 1100 (60), 3680 / 3848 (256)
-//         H = 4096: 3581 / 3836 (60: 256 blocks), 13367 / 15008 (256)
+//         H = 512: 49 / 67 (B = 1: 16 blocks)    H = 1024: 72 / 85 (32: 32)
+//         H = 2048: 99 / 119 (1: 64), 115 / 128 (32: 64)
+//         H = 4096: 289 / 317 (1: 128), 333 / 345 (32: 128)
+//   fp32  H = 512: 280 / 240 (B = 60: 32 blocks, each with the whole K)
+//         H = 2048: 1231 / 1111 (60), 3612 / 3826 (256)
+//         H = 4096: 3553 / 3801 (60: 256 blocks), 13183 / 14989 (256)
 // In fp32 a few blocks each walk all of K on the matrix units, so the grid has
 // to fill the chip unless K is short; 64 x 64 tiles take 0.9 of the time of
 // four 32 x 32 ones, so the fewer rounds of the chip decide.
@@ -655,9 +655,10 @@ static int lstm_fwd_impl(int T, int B, int D, int H, const E* x, const E* Wx, co
     for (int t = 0; t < T; ++t) {
       ktimer_begin(kSiteLstmFwdGemm, s);
       const int S = sizeof(E) == 2 ? w.plan.splits : 0;
-      launch_step_fwd(B, D, H, S, S ? cdiv((D + H) / 64, S) : 0, x + static_cast<size_t>(t) * B * D, t == 0 ? h0e : h + (t - 1) * BH, Wx, Wh, bias,
-                      t == 0 ? c0 : c + (t - 1) * BH, reset ? reset + static_cast<size_t>(t) * B : nullptr, h + t * BH,
-                      c + t * BH, gates ? gates + static_cast<size_t>(t) * B * 4 * H : nullptr, s);
+      launch_step_fwd(B, D, H, S, S ? cdiv((D + H) / 64, S) : 0, x + static_cast<size_t>(t) * B * D,
+                      t == 0 ? h0e : h + (t - 1) * BH, Wx, Wh, bias, t == 0 ? c0 : c + (t - 1) * BH,
+                      reset ? reset + static_cast<size_t>(t) * B : nullptr, h + t * BH, c + t * BH,
+                      gates ? gates + static_cast<size_t>(t) * B * 4 * H : nullptr, s);
       ktimer_end(kSiteLstmFwdGemm, s);
     }
     return check_launch("o5_lstm_fwd");

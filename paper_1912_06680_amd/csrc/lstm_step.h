@@ -1,5 +1,5 @@
 // One recurrent step of the LSTM in one launch, for small and middle batches
-// (and every batch in fp32): the step's product and its cell.
+// (in fp32 for most shapes): the step's product and its cell.
 //
 //   forward   a = [x_t | h~_{t-1}] . [W_x | W_h]^T + b, then the cell
 //   backward  R = [P_t | dG_{t+1}] . [W | W_h^T]^T, then the gate gradients
@@ -16,8 +16,8 @@
 // partial tiles meet once in LDS, are added in order, and the same threads
 // finish the cell.  In bf16 the K ranges of the partial sums and the order
 // within them are those of the separate product (gemm_plan.h), so a shape's
-// results do not depend on which of the two paths serves it; in fp32 wave w
-// takes pieces w, w + 4, ....  (Fragments loaded from memory straight into
+// results do not depend, to the bit, on which of the two paths serves it; in
+// fp32 wave w takes pieces w, w + 4, ....  (Fragments loaded from memory straight into
 // registers, 16 rows x 64 bytes with consecutive lanes on different rows,
 // took 22.8 us for a bf16 step of B = 256, D = H = 1024;
 // this form takes 12.5, the product and cell as two launches took 36.)
@@ -413,8 +413,8 @@ __global__ void __launch_bounds__(NT, 1) lstm_step_fwd(int B, int D, int H, int 
 // forward step.
 template <typename E, int T>
 __global__ void __launch_bounds__(NT, 1) lstm_step_bwd(
-    int B, int Bp, int H, int S, int kps, const E* __restrict__ P, const E* __restrict__ Wf, int K0, const E* __restrict__ dG_next,
-    const E* __restrict__ WhT, const uint8_t* __restrict__ reset_next, const float* __restrict__ dh_t,
+    int B, int Bp, int H, int S, int kps, const E* __restrict__ P, const E* __restrict__ Wf, int K0,
+    const E* __restrict__ dG_next, const E* __restrict__ WhT, const uint8_t* __restrict__ reset_next, const float* __restrict__ dh_t,
     const float* __restrict__ dh_extra, const float* dc_in, float* dc_out, const E* __restrict__ gates_t,
     const float* __restrict__ c_t, const float* __restrict__ c_prev, const uint8_t* __restrict__ reset_t,
     E* __restrict__ dG_t, float* __restrict__ db_part, int db_accumulate, E* __restrict__ dGT, size_t ldt, int col0) {
