@@ -55,8 +55,8 @@ SITE_SOURCES = {"lstm_fwd_gemm": "lstm.hip", "lstm_dh_gemm": "lstm.hip", "lstm_d
 
 
 def kernel_digest(site, csrc=None):
-    """sha256 over the source file of `site`'s kernel and the headers that it
-    includes, directly or not, in name order: what its counters depend on."""
+    """sha256 over the source file of `site`'s kernel and the headers of csrc/ that
+    it includes, directly or not, in name order: what its counters depend on."""
     import hashlib
     import re
     d = csrc or os.path.join(ROOT, "paper_1912_06680_amd", "csrc")
@@ -66,7 +66,7 @@ def kernel_digest(site, csrc=None):
         if f not in seen and os.path.exists(os.path.join(d, f)):
             with open(os.path.join(d, f), "rb") as fh:
                 seen[f] = fh.read()
-            todo += re.findall(r'^#include "([^"]+)"', seen[f].decode(), re.M)
+            todo += re.findall(r'^#include "([^"/]+)"', seen[f].decode(), re.M)
     h = hashlib.sha256()
     for f in sorted(seen):
         h.update(f.encode())
