@@ -219,6 +219,14 @@ def _short(name):
 N_XCD, N_SIMD = 8, 1024   # MI355X: 8 XCDs, 256 CUs x 4 SIMDs
 
 
+def mfma_flop(kernel):
+    """FLOPs of one matrix instruction of `kernel`: 2 x 32 x 32 x 16 in bf16, in
+    fp32 2 x 16 x 16 x 4 (the one-launch steps) or 2 x 32 x 32 x 2."""
+    if "lstm_step" in kernel and "<float" in kernel:
+        return 2.0 * 16 * 16 * 4
+    return 2.0 * 32 * 32 * 2 if "gemm_f32" in kernel else 2.0 * 32 * 32 * 16
+
+
 def counter_table(fetch_dir, write_dir, mfma_dir, trace_dir, out_md, command):
     """Per-kernel table from four rocprofv3 runs of bench.py --copy-ref:
     FETCH_SIZE and WRITE_SIZE (scaled by the reference conversion as in
@@ -258,7 +266,7 @@ def counter_table(fetch_dir, write_dir, mfma_dir, trace_dir, out_md, command):
         if m and "SQ_INSTS_MFMA" in m and mean(m["SQ_INSTS_MFMA"]) > 0:
             grbm = mean(m["GRBM_GUI_ACTIVE"]) / N_XCD
             r["mfma_instr"] = mean(m["SQ_INSTS_MFMA"])
-            r["mfma_tflops"] = r["mfma_instr"] * 32768.0 / (r["us"] * 1e-6) / 1e12
+            r["mfma_tflops"] = r["mfma_instr"] * mfma_flop(key[1]) / (r["us"] * 1e-6) / 1e12
             r["mfma_busy"] = mean(m["SQ_VALU_MFMA_BUSY_CYCLES"]) / (N_SIMD * grbm)
             r["clock_ghz"] = grbm / (r["us"] * 1e3)
         rows.append(r)
@@ -274,7 +282,8 @@ def counter_table(fetch_dir, write_dir, mfma_dir, trace_dir, out_md, command):
              f"{sf:.3f}, WRITE_SIZE x {sw:.3f}. WRITE_SIZE misses lines still dirty in the L2 when a kernel "
              f"ends, so it can read below the bytes a kernel writes. MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / "
              f"(1024 SIMDs x GRBM_GUI_ACTIVE / 8), at the clock the kernel ran at (column `GHz`); MFMA TFLOP/s = "
-             f"SQ_INSTS_MFMA x 32768 FLOP (v_mfma_f32_32x32x16_bf16) / traced time.", ""]
+             f"SQ_INSTS_MFMA x 32768 FLOP (v_mfma_f32_32x32x16_bf16; 4096 for the fp32 products' 32x32x2, 2048 for "
+             f"the fp32 steps' 16x16x4) / traced time.", ""]
     for phase, title in (("step", "## The optimizer step (warmup, instrumented and timed steps)"),
                          ("other", "## The other workloads (tiny and mid steps, LSTM forward + BPTT at B = 1024, "
                                    "rollout inference at B = 4096)")):
