@@ -121,6 +121,8 @@ int o5_lstm_fwd(o5_dtype dt, int T, int B, int D, int H,
  * dhT, dcT [B, H] fp32 or NULL (= 0): gradient arriving at the final state.
  * dWx      out [4H, D] fp32.   dWh: out [4H, H] fp32.   db: out [4H] fp32.
  * dx       out [T, B, D] dt, or NULL to skip the input gradient.
+ *          (dWx and dWh also hold transposed weights while the call's work
+ *          runs, so they are meaningful only once it is done.)
  * ws       scratch of o5_lstm_bptt_workspace_bytes(dt, T, B, D, H) bytes.
  * ------------------------------------------------------------------------ */
 size_t o5_lstm_bptt_workspace_bytes(o5_dtype dt, int T, int B, int D, int H);
